@@ -7,13 +7,11 @@
 //
 // Tiling: a workgroup (4 wavefronts) computes a 128 x 128 tile of C, each wavefront a 64 x 64
 // sub-tile as 2 x 2 blocks of 32 x 32; or, when the grid of 256 x 256 tiles still has a workgroup
-// for every compute unit, a 256 x 256 tile with 4 x 4 blocks per wavefront.  K advances 32 at a
-// time.  gemm_dma_kernel (K a multiple of 32) copies tiles global -> LDS directly into a ring of
-// three stages, two tiles ahead; gemm_kernel (any K) stages them through registers into two LDS
-// stages, one tile ahead.  Tiles are stored in LDS in MFMA fragment order (lane l of a fragment at
-// offset 16 l), so every fragment read is one conflict-free ds_read_b128 per lane.  Workgroups that
-// share a weight tile are adjacent in launch order (x over M tiles), so each weight tile is read
-// from HBM once and re-served from L2.
+// for every compute unit, a 256 x 256 tile with 4 x 4 blocks per wavefront.  gemm_tile_kernel (K a
+// multiple of 32) copies tiles global -> LDS directly into a ring of stages; gemm_kernel (any K)
+// stages them through registers into two LDS stages, one tile ahead.  Every fragment read is one
+// conflict-free ds_read_b128 per lane.  Workgroups that share a weight tile are adjacent in launch
+// order (x over M tiles), so each weight tile is read from HBM once and re-served from L2.
 //
 // The producers of A write the hi/lo pair directly: RMSNorm (before QKV and gate/up), the
 // attention output (before O) and the SwiGLU of the gate/up output (before down).
@@ -157,14 +155,15 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
 }
 
 // Copies 16 bytes per lane from global memory straight into LDS (global_load_lds_dwordx4): lane l
-// of the wavefront writes LDS bytes [lds_addr + 16 l, lds_addr + 16 l + 16).  Issued as inline
-// assembly so that the compiler does not wait for every such load before each LDS read (it cannot
-// tell which LDS bytes a DMA load writes); the kernel waits for them itself (wait_vm).  m0 holds
-// the wavefront-uniform LDS address; nothing else in the kernel uses m0.  An LDS DMA must not
-// directly follow a scalar write of m0 (gfx9 asks for one wait state there; the compiler inserts it
-// in code it generates, not inside inline assembly), hence the s_nop.
-__device__ __forceinline__ void dma16(const void *g, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_addr) : "memory");
+// of the wavefront reads base + off and writes LDS bytes [lds_addr + 16 l, lds_addr + 16 l + 16).
+// Issued as inline assembly so that the compiler does not wait for every such load before each LDS
+// read (it cannot tell which LDS bytes a DMA load writes); the kernel waits for them itself
+// (wait_vm).  m0 holds the wavefront-uniform LDS address; nothing else in the kernel uses m0.  An
+// LDS DMA must not directly follow a scalar write of m0 (gfx9 asks for one wait state there; the
+// compiler inserts it in code it generates, not inside inline assembly), hence the s_nop.
+__device__ __forceinline__ void dma16(uint32_t off, const void *base, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
+                 : "memory");
 }
 
 // s_waitcnt vmcnt(N), other counters untouched.
@@ -180,191 +179,267 @@ __device__ __forceinline__ void wait_lgkm() {
     __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
 }
 
-// The same product as gemm_kernel (same MFMAs in the same order: bit-identical results) for K a
-// multiple of 32, with the operand tiles copied into a ring of three LDS stages by
-// global_load_lds: tile t + 2 is in flight while tile t is multiplied, and no registers stage it.
-// Each wavefront computes WB x WB blocks of 32 x 32, so a workgroup tile is 64 WB square: WB = 2
-// gives the 128 x 128 tile, WB = 4 the 256 x 256 tile (16 accumulator blocks per wavefront, one
-// wavefront per SIMD), which reads half as many operand bytes per product from L2 and LDS.
-// The weight tile in LDS is row-major, four 16-byte k segments per row (BK = 32), segment s of row
-// r stored at slot 4 r + (s ^ ((r >> 2) & 3)): each DMA instruction then copies 16 rows x 64
-// contiguous bytes (lane l: row 16 q + l / 4 of instruction q), and the 32 x 32 fragment reads
-// (lane l: row l % 32, segment 2 step + l / 32) touch every LDS bank once per 16 lanes.  (Loading
-// in fragment order instead, 32 rows x 32 bytes per instruction, took 1.3-1.6x as long.)  The
-// activation tile holds a row's whole 128-byte k block (hi segments 0-3, lo segments 4-7),
-// segment g of row r at slot 8 r + (g ^ ((r >> 1) & 7)): one DMA instruction copies 8 rows x 128
-// contiguous bytes (full cache lines; 16 rows x 64 bytes of hi and of lo took 5-15% longer per
-// GEMM), and the fragment reads again meet every bank once per 16 lanes.
-//
-// With one wavefront per SIMD (WB = 4) nothing else hides the latency of a fragment read or of the
-// barrier, so that loop is software-pipelined (K >= 64): the fragments of the next k step are
-// read one whole batch of 32 MFMAs before they are used, the tile's barrier sits between its two
-// k steps, and the DMA of tile t + 2 is issued between the MFMAs of tile t's first step.  Schedule
-// fences keep the compiler from moving the MFMAs across the barrier or the reads to their use.
-template <int MODE, int WB>
-__global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs a) {
-    constexpr int S = 3;
-    constexpr int TILE = 64 * WB;                 // workgroup tile rows of each operand
-    constexpr int SLOTS = TILE * (BK / 8);        // 16-byte slots per operand tile (4 per row)
-    constexpr int AI = 2 * WB;                    // activation copies per wavefront per k tile
-    constexpr int PER_TILE = AI + WB;             // load instructions per wavefront per k tile
-    static_assert(SLOTS == 4 * WB * 64, "each wavefront loads WB instructions of the weight tile");
-    static_assert(BK == 32, "the segment swizzles assume 32-wide k tiles");
-    __shared__ uint4 lds[S][3][SLOTS];            // per stage: activation tile (2 SLOTS), weight tile
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)&lds[0][0][0];
-    const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = blockIdx.x * TILE, n0 = blockIdx.y * TILE;
-    const uint16_t *W = a.w[blockIdx.z];
-    const int M = a.M, N = a.N, K = a.K, nk = K / BK;
+// Workgroup barrier for kernels that order their LDS traffic themselves (wait_vm and wait_lgkm before
+// it); no LDS access moves across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 
-    // activation copy qa = wave * AI + i: lane l copies segment (l % 8) ^ ((row >> 1) & 7) of the
-    // 128-byte k block of row 8 qa + l / 8 into slot 64 qa + l; weight copy q = wave * WB + i: lane
-    // l copies row 16 q + l / 4, k segment (l % 4) ^ ((row >> 2) & 3) into slot 64 q + l.  Rows past
-    // M or N are clamped (in bounds), their results are never stored.
-    // SWIGLU: the weight tile's 32-row blocks alternate between Wg and Wu rows n0 / 2 + 32 (b / 2) ..
-    const uint16_t *src_a[AI], *src_w[WB];
+// Workgroup tile of gemm_tile_kernel: 4 wavefronts as WM x WN, each MB x NB blocks of 32 x 32; K
+// advances BK (32 or 64) at a time through S stages of LDS.
+template <int WM_, int WN_, int MB_, int NB_, int BK_, int S_>
+struct Tile {
+    static constexpr int WM = WM_, WN = WN_, MB = MB_, NB = NB_, TK = BK_, S = S_;
+    static constexpr int TM = 32 * WM * MB, TN = 32 * WN * NB;   // rows of the activation and weight tiles
+    static constexpr int STEPS = TK / 16;                        // MFMA k steps per k tile
+    static constexpr int A_BYTES = TM * TK * 4, W_BYTES = TN * TK * 2, STAGE = A_BYTES + W_BYTES;
+    static constexpr int AI = A_BYTES / 4096, WI = W_BYTES / 4096, D = AI + WI;   // copies per wavefront per k tile
+    static constexpr int LDS = S * STAGE;
+    static_assert(WM * WN == 4 && (TK == 32 || TK == 64) && S >= 2, "four wavefronts");
+    static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
+};
+
+// The same product as gemm_kernel (same MFMAs in the same order for every tile shape: bit-identical
+// results) for K a multiple of TK, with the operand tiles copied into a ring of S LDS stages by
+// global_load_lds, so that no registers stage them.
+//
+// LDS layout.  Both tiles hold 128-byte rows of eight 16-byte segments (weights: 64 k; activation:
+// the hi and lo of 32 k, one sub-tile per 32 k), segment g of row r at slot 8 r + (g ^ ((r >> 1) &
+// 7)): one copy instruction moves 8 rows x 128 contiguous bytes (full cache lines), and the 32 x 32
+// fragment reads (lane l: row l % 32, 8 k at l / 32) touch every LDS bank once per 16 lanes.  With
+// TK = 32 a weight row is 64 bytes, four segments, segment s of row r at slot 4 r + (s ^ ((r >> 2)
+// & 3)): 16 rows x 64 bytes per copy.
+//
+// Pipeline.  One wavefront per SIMD with the large tiles: nothing else hides a wavefront's stalls, so
+// the instruction order is fixed by hand.  While the MFMAs of one 16-deep k step run, the fragments
+// of the next are read into a second register set and a share of the copies of a later tile is
+// issued, each behind an MFMA of its own (schedule fences keep them there): copies issued three in
+// a row, and a step's fragment reads in one burst ahead of its MFMAs, had left the matrix pipe idle
+// while all four wavefronts queued at the LDS and texture units (8192 rows of the 70B-shaped layer,
+// before -> now: gate/up 12.06 -> 11.1 ms, down 5.87 -> 5.24, QKV 2.12 -> 1.91; pipe busy 66 ->
+// 82-91% of the cycles, the clock falling from 1.82 to 1.6 GHz: the power limit is the bound now.
+// 1024 rows of the 8B-shaped layer, 128 x 128 tiles: down 277 -> 211 us, O 84 -> 66).
+// The barrier of tile t stands before its last step, by when every wavefront has read its last
+// fragment of the tile: the stage then takes tile t + S, whose copies are issued over that last
+// step and the first steps of tile t + 1; what the barrier waits for is tile t + 1, issued S - 1
+// tiles before.
+template <int MODE, class C>
+__global__ __launch_bounds__(256, 1) void gemm_tile_kernel(GemmArgs a) {
+    constexpr int MB = C::MB, NB = C::NB, S = C::S, TK = C::TK, STEPS = C::STEPS;
+    constexpr int AI = C::AI, WI = C::WI, D = C::D;
+    __shared__ __align__(16) char lds[C::LDS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    const int wm = wave / C::WN, wn = wave % C::WN;
+    const int m0 = blockIdx.x * C::TM, n0 = blockIdx.y * C::TN;
+    const int M = a.M, N = a.N, K = a.K, nk = K / TK;
+
+    // Copies of this wavefront: uniform bases that advance with the tile, and a 32-bit byte offset
+    // per lane.  Activation copy q = wave * AI + i: 8 rows of sub-tile q / (TM / 8); weight copy q =
+    // wave * WI + i.  Rows past M or N are clamped (in bounds), their results are never stored.
+    // SWIGLU: the weight tile's rows alternate between Wg and Wu rows n0 / 2 .., 32 of each at a
+    // time (16 with one 32-wide block per wavefront, so that each block holds its own pairs).
+    constexpr int HALF = NB % 2 == 0 ? 32 : 16;
+    const char *const base_a = reinterpret_cast<const char *>(a.a + (size_t)m0 * a.lda);
+    const int nrow0 = MODE == GEMM_SWIGLU ? n0 / 2 : n0;
+    const char *const base_w =
+        reinterpret_cast<const char *>(a.w[MODE == GEMM_SWIGLU ? 0 : blockIdx.z] + (size_t)nrow0 * K);
+    const long up = MODE == GEMM_SWIGLU ? reinterpret_cast<const char *>(a.w[1]) - reinterpret_cast<const char *>(a.w[0]) : 0;
+    uint32_t off_a[AI], off_w[WI];
 #pragma unroll
     for (int i = 0; i < AI; ++i) {
-        const int r = 8 * (wave * AI + i) + (lane >> 3), g = (lane & 7) ^ ((r >> 1) & 7);
-        src_a[i] = a.a + (size_t)min(m0 + r, M - 1) * a.lda + 8 * g;
+        const int q = wave * AI + i, sub = q / (C::TM / 8), r = 8 * (q % (C::TM / 8)) + (lane >> 3);
+        const int g = (lane & 7) ^ ((r >> 1) & 7);
+        off_a[i] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)a.lda * 2 + 128 * sub + 16 * g;
     }
+    long mat[WI];   // where the matrix of copy i's rows begins (wavefront-uniform)
 #pragma unroll
-    for (int i = 0; i < WB; ++i) {
-        const int q = wave * WB + i, r = 16 * q + (lane >> 2), seg = (lane & 3) ^ ((r >> 2) & 3);
-        if (MODE == GEMM_SWIGLU) {
-            const int b = r >> 5, n = min(n0 / 2 + 32 * (b >> 1) + (r & 31), N - 1);
-            src_w[i] = a.w[b & 1] + (size_t)n * K + 8 * seg;
-        } else {
-            src_w[i] = W + (size_t)min(n0 + r, N - 1) * K + 8 * seg;
-        }
+    for (int i = 0; i < WI; ++i) {
+        const int q = wave * WI + i;
+        const int r = TK == 64 ? 8 * q + (lane >> 3) : 16 * q + (lane >> 2);
+        const int seg = TK == 64 ? (lane & 7) ^ ((r >> 1) & 7) : (lane & 3) ^ ((r >> 2) & 3);
+        const int n = MODE == GEMM_SWIGLU ? r / (2 * HALF) * HALF + r % HALF : r;
+        mat[i] = MODE == GEMM_SWIGLU ? ((TK == 64 ? 8 : 16) * q / HALF & 1) * up : 0;
+        off_w[i] = (uint32_t)min(n, N - 1 - nrow0) * (uint32_t)K * 2 + 16 * seg;
     }
-    // this wavefront's share of tile t, part i: activation copies 2 i and 2 i + 1, weight copy i
-    auto issue_part = [&](int t, int i) {
-        const int st = t % S, q = wave * WB + i, qa = wave * AI + 2 * i;
-        dma16(src_a[2 * i] + 64 * t, lds_base + ((st * 3) * SLOTS + qa * 64) * 16);
-        dma16(src_a[2 * i + 1] + 64 * t, lds_base + ((st * 3) * SLOTS + (qa + 1) * 64) * 16);
-        dma16(src_w[i] + BK * t, lds_base + ((st * 3 + 2) * SLOTS + q * 64) * 16);
+    // copy d of tile t into stage st
+    auto copy = [&](int t, int st, int d) {
+        if (d < AI)
+            dma16(off_a[d], base_a + (size_t)t * (TK * 4), lds_base + st * C::STAGE + (wave * AI + d) * 1024);
+        else
+            dma16(off_w[d - AI], base_w + mat[d - AI] + (size_t)t * (TK * 2),
+                  lds_base + st * C::STAGE + C::A_BYTES + (wave * WI + d - AI) * 1024);
     };
-    auto issue = [&](int t) {
-#pragma unroll
-        for (int i = 0; i < WB; ++i) issue_part(t, i);
-    };
+    // the copies of one tile are issued in STEPS shares
+    constexpr auto share = [](int s) { return s * D / STEPS; };
 
-    f32x16 acc[WB][WB];
+    f32x16 acc[MB][NB];
 #pragma unroll
-    for (int i = 0; i < WB; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < WB; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
+    // byte offsets of this lane's fragments in a stage, without the block and the sub-tile
     const int fr = lane & 31, fk = lane >> 5;   // fragment row and k half of this lane
-    // the fragments of k step `step` (0 or 1) of tile t, which is in stage t % S
-    auto read = [&](int t, int step, bf16x8 (&ah)[WB], bf16x8 (&al)[WB], bf16x8 (&bw)[WB]) {
-        const uint4 *L = &lds[t % S][0][0];
-        const int seg = 2 * step + fk;
+    int ao[2][2], wo[STEPS];
 #pragma unroll
-        for (int b = 0; b < WB; ++b) {
-            const int ra = 32 * (wm * WB + b) + fr, rb = 32 * (wn * WB + b) + fr;
-            const int sw = (ra >> 1) & 7;
-            const int sb = 4 * rb + (seg ^ ((rb >> 2) & 3));
-            ah[b] = as_bf16x8(L[8 * ra + (seg ^ sw)]);
-            al[b] = as_bf16x8(L[8 * ra + ((4 + seg) ^ sw)]);
-            bw[b] = as_bf16x8(L[2 * SLOTS + sb]);
-        }
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int hl = 0; hl < 2; ++hl)
+            ao[p][hl] = 128 * (32 * wm * MB + fr) + 16 * ((2 * p + fk + 4 * hl) ^ ((fr >> 1) & 7));
+#pragma unroll
+    for (int p = 0; p < STEPS; ++p)
+        wo[p] = TK == 64 ? 128 * (32 * wn * NB + fr) + 16 * ((2 * p + fk) ^ ((fr >> 1) & 7))
+                         : 64 * (32 * wn * NB + fr) + 16 * ((2 * p + fk) ^ ((fr >> 2) & 3));
+    struct Frags {
+        bf16x8 ah[MB], al[MB], bw[NB];
     };
-    // one k step of accumulator row i: hi then lo into each block
-    auto mma_row = [&](int i, const bf16x8 (&ah)[WB], const bf16x8 (&al)[WB], const bf16x8 (&bw)[WB]) {
-#pragma unroll
-        for (int j = 0; j < WB; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bw[j], acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], bw[j], acc[i][j], 0, 0, 0);
-        }
+    // fragment r of k step p, in the order the step's MFMAs need them: the first row's hi and lo
+    // with the weight blocks, then the other rows
+    constexpr int RD = 2 * MB + NB;
+    auto read = [&](const char *L, int p, int r, Frags &f) {
+        auto ld = [&](int o) { return as_bf16x8(*reinterpret_cast<const uint4 *>(L + o)); };
+        const int sub = C::TM * 128 * (p >> 1);
+        if (r == 0) f.ah[0] = ld(ao[p & 1][0] + sub);
+        else if (r <= NB) f.bw[r - 1] = ld(C::A_BYTES + wo[p] + 32 * (TK * 2) * (r - 1));
+        else if (r == NB + 1) f.al[0] = ld(ao[p & 1][1] + sub);
+        else if ((r - NB) % 2 == 0) f.ah[(r - NB) / 2] = ld(ao[p & 1][0] + sub + 4096 * ((r - NB) / 2));
+        else f.al[(r - NB) / 2] = ld(ao[p & 1][1] + sub + 4096 * ((r - NB) / 2));
+    };
+    // MFMA q of a step: rows of blocks in turn, hi then lo into each block
+    constexpr int MM = 2 * MB * NB;
+    auto mma = [&](int q, const Frags &f) {
+        const int i = q / (2 * NB), j = q / 2 % NB;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q & 1 ? f.al[i] : f.ah[i], f.bw[j], acc[i][j], 0, 0, 0);
     };
 
-    if constexpr (WB != 4) {
-        issue(0);
-        if (nk > 1) issue(1);
-        for (int t = 0; t < nk; ++t) {
-            // tile t has landed when at most the next tile's loads are still in flight
-            if (t + 1 < nk) wait_vm<PER_TILE>();
-            else wait_vm<0>();
-            __syncthreads();  // every wavefront's part of tile t is in LDS; stage (t - 1) % S is free
-            if (t + 2 < nk) issue(t + 2);
+    Frags fa, fb;
+    int st = 0;   // stage of the tile being multiplied
+    // one step: the MFMAs of `cur`; the fragments of the next step (of stage Ln) into `nxt`; the
+    // copies d0 .. d1 - 1 of tile tc into stage sc
+    auto step = [&](const Frags &cur, Frags &nxt, const char *Ln, int pn, auto reads, int tc, int sc, auto d0, auto d1) {
+        constexpr int R = decltype(reads)::value ? RD : 0, ND = decltype(d1)::value - decltype(d0)::value;
+        constexpr int RW = MM >= 8 ? MM - MM / 4 : MM;   // the reads go out behind the first three quarters
 #pragma unroll
-            for (int step = 0; step < BK / 16; ++step) {
-                bf16x8 ah[WB], al[WB], bw[WB];
-                read(t, step, ah, al, bw);
+        for (int q = 0; q < MM; ++q) {
+            mma(q, cur);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < WB; ++i) mma_row(i, ah, al, bw);
-            }
+            for (int r = 0; r < R; ++r)
+                if (r * RW / (R ? R : 1) == q) read(Ln, pn, r, nxt);
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+                if ((2 * d + 1) * MM / (2 * (ND ? ND : 1)) == q) copy(tc, sc, decltype(d0)::value + d);
+            __builtin_amdgcn_sched_barrier(0);
         }
-    } else {
-        // nk >= 2 (launch_gemm_mode).  The loop body is straight-line (the last two tiles are
-        // peeled), so that no merge of control flow makes the second batch wait for the reads
-        // issued after the barrier.
-        issue(0);
-        issue(1);
-        wait_vm<PER_TILE>();
-        __syncthreads();
-        bf16x8 h0[WB], l0[WB], w0[WB], h1[WB], l1[WB], w1[WB];
-        read(0, 0, h0, l0, w0);
-        auto tile = [&](int t, auto more_dma, auto more_tiles) {
-            read(t, 1, h1, l1, w1);
-            __builtin_amdgcn_sched_barrier(0);
-            // the DMA of tile t + 2 goes to stage (t + 2) % S, which held tile t - 1: every
-            // wavefront finished reading it before the previous tile's barrier
+    };
+    using std::integral_constant;
+    constexpr integral_constant<int, 0> zero{};
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    // Tile t (stage st).  FIRST: the rest of tile t + S - 1's copies go out over the first steps;
+    // LAST: tile t + S's first share over the last step; AHEAD: tiles issued past t + 1 when the
+    // barrier waits for t + 1, or -1: t is the last tile (no barrier, no reads past it).
+    auto tile = [&](int t, auto first, auto last, auto ahead) {
+        constexpr bool FIRST = decltype(first)::value, LAST = decltype(last)::value;
+        constexpr int AHEAD = decltype(ahead)::value;
+        const char *L = lds + st * C::STAGE;
+        const int stn = st + 1 == S ? 0 : st + 1, stp = st == 0 ? S - 1 : st - 1;
+        const char *Ln = lds + stn * C::STAGE;
+#define STG_STEP(P, CUR, NXT)                                                                                     \
+    step(CUR, NXT, L, (P) + 1, yes, t + S - 1, stp, integral_constant<int, FIRST ? share((P) + 1) : 0>{},         \
+         integral_constant<int, FIRST ? share((P) + 2) : 0>{})
+        STG_STEP(0, fa, fb);
+        if constexpr (STEPS == 4) {
+            STG_STEP(1, fb, fa);
+            STG_STEP(2, fa, fb);
+        }
+#undef STG_STEP
+        if constexpr (AHEAD >= 0) {
+            wait_vm<(AHEAD >= 0 ? AHEAD : 0) * D>();   // this wavefront's copies of tile t + 1 have landed
+            wait_lgkm<0>();                            // and its reads of tile t are done
+            lds_barrier();
+            step(fb, fa, Ln, 0, yes, t + S, st, zero, integral_constant<int, LAST ? share(1) : 0>{});
+        } else {
+            step(fb, fa, Ln, 0, no, 0, 0, zero, zero);
+        }
+        st = stn;
+    };
+    auto first_frags = [&]() {
 #pragma unroll
-            for (int i = 0; i < WB; ++i) {
-                mma_row(i, h0, l0, w0);
-                if constexpr (decltype(more_dma)::value) issue_part(t + 2, i);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (decltype(more_tiles)::value) {
-                if constexpr (decltype(more_dma)::value) wait_vm<PER_TILE>();   // tile t + 1 has landed
-                else wait_vm<0>();
-                wait_lgkm<0>();   // this wavefront's reads of tile t are done
-                __syncthreads();
-                read(t + 1, 0, h0, l0, w0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        for (int r = 0; r < RD; ++r) read(lds, 0, r, fa);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto tail = [&](auto self, int t, auto j) -> void {   // tiles nk - S + j .. nk - 1
+        constexpr int J = decltype(j)::value;
+        tile(t, integral_constant<bool, J == 0>{}, no, integral_constant<int, S - 2 - J>{});
+        if constexpr (J + 1 < S) self(self, t + 1, integral_constant<int, J + 1>{});
+    };
+    if (nk >= S) {
 #pragma unroll
-            for (int i = 0; i < WB; ++i) mma_row(i, h1, l1, w1);
-            __builtin_amdgcn_sched_barrier(0);
-        };
+        for (int u = 0; u < S; ++u)
+#pragma unroll
+            for (int d = 0; d < (u < S - 1 ? D : share(1)); ++d) copy(u, u, d);
+        wait_vm<(S - 2) * D + share(1)>();
+        lds_barrier();
+        first_frags();
         int t = 0;
-        for (; t + 2 < nk; ++t) tile(t, std::true_type{}, std::true_type{});
-        tile(t, std::false_type{}, std::true_type{});
-        tile(t + 1, std::false_type{}, std::false_type{});
+        for (; t < nk - S; ++t) tile(t, yes, yes, integral_constant<int, S - 2>{});
+        tail(tail, t, zero);
+    } else {   // fewer tiles than stages: all copied at once
+        for (int u = 0; u < nk; ++u)
+#pragma unroll
+            for (int d = 0; d < D; ++d) copy(u, u, d);
+        wait_vm<0>();
+        lds_barrier();
+        first_frags();
+        for (int t = 0; t + 1 < nk; ++t) tile(t, no, no, zero);
+        tile(nk - 1, no, no, integral_constant<int, -1>{});
     }
 
-    if (MODE == GEMM_SWIGLU) {   // blocks j (gate) and j + 1 (up) hold the same rows of h
+    if constexpr (MODE == GEMM_SWIGLU) {
+        auto put = [&](int m, int n, float gt, float up) {
+            if (m >= M || n >= N) return;
+            const size_t o = (size_t)m * a.ldo + pair_at(n);
+            split_pair(gt / (1.f + expf(-gt)) * up, a.out_pair[o], a.out_pair[o + 32]);
+        };
 #pragma unroll
-        for (int i = 0; i < WB; ++i)
+        for (int i = 0; i < MB; ++i) {
+            const int mb = m0 + 32 * (wm * MB + i) + 4 * (lane >> 5);
+            if constexpr (NB % 2 == 0) {   // blocks j (gate) and j + 1 (up) hold the same rows of h
 #pragma unroll
-            for (int j = 0; j < WB; j += 2) {
-                const int n = n0 / 2 + 32 * ((wn * WB + j) >> 1) + (lane & 31);
-                if (n >= N) continue;
+                for (int j = 0; j < NB; j += 2)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int m = m0 + wm * 32 * WB + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    if (m >= M) continue;
-                    const float gt = acc[i][j][r], up = acc[i][j + 1][r];
-                    const size_t o = (size_t)m * a.ldo + pair_at(n);
-                    split_pair(gt / (1.f + expf(-gt)) * up, a.out_pair[o], a.out_pair[o + 32]);
-                }
+                    for (int r = 0; r < 16; ++r)
+                        put(mb + 8 * (r >> 2) + (r & 3), n0 / 2 + 16 * (wn * NB + j) + (lane & 31), acc[i][j][r],
+                            acc[i][j + 1][r]);
+            } else {                       // columns c (gate) and c + 16 (up) of every block
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float other = lane_xor(acc[i][j][r], 16);
+                        if ((lane & 16) == 0)
+                            put(mb + 8 * (r >> 2) + (r & 3), n0 / 2 + 16 * (wn * NB + j) + (lane & 15), acc[i][j][r], other);
+                    }
             }
+        }
         return;
     }
     const int col_off = a.out_col[blockIdx.z];
 #pragma unroll
-    for (int i = 0; i < WB; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < WB; ++j) {
-            const int n = n0 + wn * 32 * WB + j * 32 + (lane & 31);
+        for (int j = 0; j < NB; ++j) {
+            const int n = n0 + 32 * (wn * NB + j) + (lane & 31);
             if (n >= N) continue;
-            store_block<MODE>(a, acc[i][j], m0 + wm * 32 * WB + i * 32, M, col_off + n, lane);
+            store_block<MODE>(a, acc[i][j], m0 + 32 * (wm * MB + i), M, col_off + n, lane);
         }
 }
 
@@ -469,6 +544,10 @@ int grid_for(size_t count) {
     return (int)(g < 8192 ? g : 8192);
 }
 
+using Tile256 = Tile<2, 2, 4, 4, 32, 3>;      // 256 x 256
+using Tile128 = Tile<2, 2, 2, 2, 64, 3>;      // 128 x 128
+using Tile128K32 = Tile<2, 2, 2, 2, 32, 3>;   // 128 x 128, K an odd multiple of 32
+
 template <int MODE>
 void launch_gemm_mode(const GemmArgs &a, int n_mats, hipStream_t st) {
     // SWIGLU tiles span the rows of both matrices: 2N virtual rows, one grid layer
@@ -481,11 +560,13 @@ void launch_gemm_mode(const GemmArgs &a, int n_mats, hipStream_t st) {
             return;
         }
     }
-    // the wide tiles when they still fill every compute unit (their pipelined loop takes K >= 64)
-    if ((long)wide.x * wide.y * wide.z >= device_compute_units() && a.K >= 2 * BK)
-        STG_LAUNCH((gemm_dma_kernel<MODE, 4>), wide, dim3(256), 0, st, a);
+    // the wide tiles when they still fill every compute unit
+    if ((long)wide.x * wide.y * wide.z >= device_compute_units())
+        STG_LAUNCH((gemm_tile_kernel<MODE, Tile256>), wide, dim3(256), 0, st, a);
+    else if (a.K % 64 == 0)
+        STG_LAUNCH((gemm_tile_kernel<MODE, Tile128>), grid, dim3(256), 0, st, a);
     else
-        STG_LAUNCH((gemm_dma_kernel<MODE, 2>), grid, dim3(256), 0, st, a);
+        STG_LAUNCH((gemm_tile_kernel<MODE, Tile128K32>), grid, dim3(256), 0, st, a);
 }
 
 }  // namespace

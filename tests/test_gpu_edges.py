@@ -229,6 +229,20 @@ def test_prefill_gemm_shortest_pipelined_k_loops(shape):
     _check(f"{shape.name} prefill 2000", _run(shape, plan, False, 5, 2048))
 
 
+# Prefill GEMM pipeline edges: k loops of 1 to 6 tiles around the three-stage LDS ring (hidden 32 and
+# 160: 32-wide k tiles, 1 and 5 of them; 64, 128, 192, 320: 64-wide, 1, 2, 3 and 5; ffn 96 and 160
+# again 32-wide, 3 and 5; ffn 384: 6 of 64), with rows just below, at and past a 128-row tile.
+GEMM_EDGES = [synth.StageShape(f"gemm-1L-h{h}-f{f}", 40 + i, 1, h, 2, 1, 64, f)
+              for i, (h, f) in enumerate([(32, 96), (64, 160), (128, 64), (160, 384), (192, 320), (320, 128)])]
+
+
+@pytest.mark.parametrize("shape", GEMM_EDGES, ids=[s.name for s in GEMM_EDGES])
+def test_prefill_gemm_k_loops_around_the_ring(shape):
+    _gpu()
+    for rows in (2, 127, 128, 130):
+        _check(f"{shape.name} prefill {rows}", _run(shape, [("prefill", rows)], False, 60, 136))
+
+
 # Every attention instance the library builds (query heads per KV head G in 1, 2, 4, 8; head
 # width 64 or 128; bf16 or fp32 cache): one small layer, prefill 70 (three 32-key tiles, ragged;
 # a 128-row query block of 128 / G positions) then two decode steps at contexts 71 and 72 (two
