@@ -181,7 +181,13 @@ __device__ __forceinline__ void attn_decode_task(const AttnArgs &a, int split, i
         if (FINAL) {
             const float o_sum = ((sm.o[0][h][c] + sm.o[1][h][c]) + sm.o[2][h][c]) + sm.o[3][h][c];
             const float l_sum = ((sm.wl[0][h] + sm.wl[1][h]) + sm.wl[2][h]) + sm.wl[3][h];
-            a.out[row * q_ld + (size_t)(g * G + h) * D + c] = o_sum / l_sum;
+            const int col = (g * G + h) * D + c;
+            if (a.out_pair) {
+                uint16_t *p = a.out_pair + row * a.out_pair_ld + pair_at(col);
+                split_pair(o_sum / l_sum, p[0], p[32]);
+            } else {
+                a.out[row * q_ld + col] = o_sum / l_sum;
+            }
             continue;
         }
         const size_t pi = ((size_t)row * hq_total + g * G + h) * a.max_splits + split;
@@ -428,8 +434,10 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
             O.w = fmaf(w, oi.w, O.w);
         }
     }
-    *reinterpret_cast<float4 *>(a.out + (size_t)row * hq_total * D + (size_t)hq * D + 4 * cg) =
-        make_float4(O.x / L, O.y / L, O.z / L, O.w / L);
+    const float4 v = make_float4(O.x / L, O.y / L, O.z / L, O.w / L);
+    const int col = hq * D + 4 * cg;
+    if (a.out_pair) store_pair4(a.out_pair + row * a.out_pair_ld + pair_at(col), v);
+    else *reinterpret_cast<float4 *>(a.out + (size_t)row * hq_total * D + col) = v;
 }
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -599,9 +607,16 @@ __global__ __launch_bounds__(256) void attn_decode_mfma(AttnArgs a) {
             const int h = 4 * lq + i;
             if (h >= G) continue;
             const float l_sum = ((wl[0][h] + wl[1][h]) + wl[2][h]) + wl[3][h];
-            float *op = a.out + (size_t)row * hq_total * D + (size_t)(g * G + h) * D;
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) op[32 * wave + 16 * nb + l16] = o[nb][i] / l_sum;
+            for (int nb = 0; nb < 2; ++nb) {
+                const int col = (g * G + h) * D + 32 * wave + 16 * nb + l16;
+                if (a.out_pair) {
+                    uint16_t *p = a.out_pair + row * a.out_pair_ld + pair_at(col);
+                    split_pair(o[nb][i] / l_sum, p[0], p[32]);
+                } else {
+                    a.out[(size_t)row * hq_total * D + col] = o[nb][i] / l_sum;
+                }
+            }
         }
         return;
     }

@@ -1,4 +1,5 @@
 // RoPE and KV-cache store, block-table updates and dense <-> paged KV copies.
+#include "part_sum.h"
 #include "stage_kernels.h"
 
 namespace stg {
@@ -12,51 +13,62 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
     return (uint16_t)(u >> 16);
 }
 
-__device__ __forceinline__ void store_kv(void *pool, size_t e, float v, int kv_fp32) {
-    if (kv_fp32)
-        static_cast<float *>(pool)[e] = v;
-    else
-        static_cast<uint16_t *>(pool)[e] = to_bf16(v);
+// Four consecutive values at element e of the cache.
+__device__ __forceinline__ void store_kv4(void *pool, size_t e, float4 v, int kv_fp32) {
+    if (kv_fp32) {
+        *reinterpret_cast<float4 *>(static_cast<float *>(pool) + e) = v;
+    } else {
+        *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(pool) + e) =
+            make_uint2(to_bf16(v.x) | ((uint32_t)to_bf16(v.y) << 16), to_bf16(v.z) | ((uint32_t)to_bf16(v.w) << 16));
+    }
 }
 
-// One workgroup per row: rotate q and k (pairs (i, i + d/2) by p * theta^(-2i/d), from the
-// per-position cos/sin tables), write rotated q, and store rotated k and v into the row's
-// position of the paged cache in the KV element type.
+// Rotates q and k (pairs (i, i + d/2) by p * theta^(-2i/d), from the per-position cos/sin tables),
+// writes rotated q, and stores rotated k and v into the row's position of the paged cache in the KV
+// element type.  A thread takes four neighbouring pairs of a q or k head, or four values of a v head
+// (d % 8 == 0), of row blockIdx.x; SP > 1: it adds the projection's partial products first.  Bound by
+// its bytes at many rows (1200 rows of the 13B-shaped stage, fp32 cache: 41 -> 28 us with 16-byte
+// accesses), by two dependent loads (metadata, then the cache position) at few: a row over several
+// workgroups instead of one takes 8.4 -> 4.0 us at 37 rows of the 8B-shaped stage.
+template <int SP>
 __global__ __launch_bounds__(256) void rope_kv_kernel(RopeKvArgs a) {
     const int row = blockIdx.x;
+    const int d = a.kv.head_dim, half = d / 2, per = half / 4;   // threads per q or k head
+    const int hq = a.n_q_heads, hkv = a.kv.n_kv_heads;
+    const int t = blockIdx.y * 256 + threadIdx.x, rot = (hq + hkv) * per;
+    if (t >= rot + hkv * 2 * per) return;
+    const size_t ld = (size_t)(hq + 2 * hkv) * d, stride = (size_t)a.rows * ld;
+    const float *src = a.qkv + row * ld;
     const int sidx = row / a.meta->rows_per_seq;
     const int pos = a.meta->pos0[sidx] + row % a.meta->rows_per_seq;
     const int slot = a.meta->seq_slot[sidx];
-    const int d = a.kv.head_dim, half = d / 2;
-    const int hq = a.n_q_heads, hkv = a.kv.n_kv_heads;
-    const size_t ld = (size_t)(hq + 2 * hkv) * d;
-    const float *src = a.qkv + row * ld;
-    const float *cs = a.cos_t + (size_t)pos * half;
-    const float *sn = a.sin_t + (size_t)pos * half;
-    const int block = a.kv.block_table[(size_t)slot * a.kv.max_blocks + pos / kBlockTokens];
-    const size_t kbase = (size_t)block * 2 * hkv * kBlockTokens * d + (size_t)(pos % kBlockTokens) * d;
     const size_t head_stride = (size_t)kBlockTokens * d;
-
-    for (int i = threadIdx.x; i < (hq + hkv) * half; i += blockDim.x) {
-        const int h = i / half, j = i % half;
-        const float x1 = src[h * d + j], x2 = src[h * d + j + half];
-        const float c = cs[j], s = sn[j];
-        const float r1 = x1 * c - x2 * s;
-        const float r2 = x1 * s + x2 * c;
-        if (h < hq) {
-            float *q = a.q_out + row * (size_t)hq * d + h * d;
-            q[j] = r1;
-            q[j + half] = r2;
-        } else {
-            const size_t e = kbase + (size_t)(h - hq) * head_stride;
-            store_kv(a.kv.pool, e + j, r1, a.kv_fp32);
-            store_kv(a.kv.pool, e + j + half, r2, a.kv_fp32);
-        }
+    auto cache = [&]() {   // the row's position of head 0 of K
+        const int block = a.kv.block_table[(size_t)slot * a.kv.max_blocks + pos / kBlockTokens];
+        return (size_t)block * 2 * hkv * head_stride + (size_t)(pos % kBlockTokens) * d;
+    };
+    if (t >= rot) {
+        const int i = 4 * (t - rot), g = i / d, c = i % d;
+        const float4 v = part_sum<SP>(src + (size_t)(hq + hkv) * d + i, stride);
+        store_kv4(a.kv.pool, cache() + (size_t)(hkv + g) * head_stride + c, v, a.kv_fp32);
+        return;
     }
-    for (int i = threadIdx.x; i < hkv * d; i += blockDim.x) {
-        const int g = i / d, c = i % d;
-        const size_t e = kbase + (size_t)(hkv + g) * head_stride + c;
-        store_kv(a.kv.pool, e, src[(size_t)(hq + hkv) * d + i], a.kv_fp32);
+    const int h = t / per, j = 4 * (t % per);
+    const float4 x1 = part_sum<SP>(src + h * d + j, stride), x2 = part_sum<SP>(src + h * d + j + half, stride);
+    const float4 c = *reinterpret_cast<const float4 *>(a.cos_t + (size_t)pos * half + j);
+    const float4 s = *reinterpret_cast<const float4 *>(a.sin_t + (size_t)pos * half + j);
+    const float4 r1 = make_float4(x1.x * c.x - x2.x * s.x, x1.y * c.y - x2.y * s.y, x1.z * c.z - x2.z * s.z,
+                                  x1.w * c.w - x2.w * s.w);
+    const float4 r2 = make_float4(x1.x * s.x + x2.x * c.x, x1.y * s.y + x2.y * c.y, x1.z * s.z + x2.z * c.z,
+                                  x1.w * s.w + x2.w * c.w);
+    if (h < hq) {
+        float *q = a.q_out + row * (size_t)hq * d + h * d + j;
+        *reinterpret_cast<float4 *>(q) = r1;
+        *reinterpret_cast<float4 *>(q + half) = r2;
+    } else {
+        const size_t e = cache() + (size_t)(h - hq) * head_stride + j;
+        store_kv4(a.kv.pool, e, r1, a.kv_fp32);
+        store_kv4(a.kv.pool, e + half, r2, a.kv_fp32);
     }
 }
 
@@ -158,7 +170,17 @@ hipError_t launch_kv_park(const KvParkArgs &a, hipStream_t st) {
 
 hipError_t launch_rope_kv_store(const RopeKvArgs &a, hipStream_t st) {
     if (a.rows <= 0) return hipSuccess;
-    STG_LAUNCH(rope_kv_kernel, dim3(a.rows), dim3(256), 0, st, a);
+    const int d = a.kv.head_dim, threads = (a.n_q_heads + a.kv.n_kv_heads) * (d / 8) + a.kv.n_kv_heads * (d / 4);
+    if (d % 8 != 0) return hipErrorInvalidValue;
+    const dim3 grid(a.rows, (threads + 255) / 256);
+    switch (a.n_part) {
+        case 1: STG_LAUNCH(rope_kv_kernel<1>, grid, dim3(256), 0, st, a); break;
+        case 2: STG_LAUNCH(rope_kv_kernel<2>, grid, dim3(256), 0, st, a); break;
+        case 3: STG_LAUNCH(rope_kv_kernel<3>, grid, dim3(256), 0, st, a); break;
+        case 4: STG_LAUNCH(rope_kv_kernel<4>, grid, dim3(256), 0, st, a); break;
+        case 8: STG_LAUNCH(rope_kv_kernel<8>, grid, dim3(256), 0, st, a); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -17,10 +17,12 @@
 // attention output (before O) and the SwiGLU of the gate/up output (before down).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "lanes.h"
 #include "pair.h"
+#include "part_sum.h"
 #include "stage_kernels.h"
 
 namespace stg {
@@ -161,9 +163,15 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
 // (wait_vm).  m0 holds the wavefront-uniform LDS address; nothing else in the kernel uses m0.  An
 // LDS DMA must not directly follow a scalar write of m0 (gfx9 asks for one wait state there; the
 // compiler inserts it in code it generates, not inside inline assembly), hence the s_nop.
+// NT: non-temporal, for bytes that no other workgroup reads.
+template <bool NT = false>
 __device__ __forceinline__ void dma16(uint32_t off, const void *base, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
-                 : "memory");
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "s"(lds_addr)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
+                     : "memory");
 }
 
 // s_waitcnt vmcnt(N), other counters untouched.
@@ -189,10 +197,14 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
+constexpr int kTurn = 896;   // a whole number of the gate/up rows of any tile: 56, 64 or 128
+
 // Workgroup tile of gemm_tile_kernel: 4 wavefronts as WM x WN, each MB x NB blocks of 32 x 32; K
-// advances BK (32 or 64) at a time through S stages of LDS.
-template <int WM_, int WN_, int MB_, int NB_, int BK_, int S_>
+// advances BK (32 or 64) at a time through S stages of LDS.  ONE: calls of at most TM rows, whose
+// weights no other workgroup reads.
+template <int WM_, int WN_, int MB_, int NB_, int BK_, int S_, bool ONE_ = false>
 struct Tile {
+    static constexpr bool ONE = ONE_;
     static constexpr int WM = WM_, WN = WN_, MB = MB_, NB = NB_, TK = BK_, S = S_;
     static constexpr int TM = 32 * WM * MB, TN = 32 * WN * NB;   // rows of the activation and weight tiles
     static constexpr int STEPS = TK / 16;                        // MFMA k steps per k tile
@@ -227,7 +239,10 @@ struct Tile {
 // fragment of the tile: the stage then takes tile t + S, whose copies are issued over that last
 // step and the first steps of tile t + 1; what the barrier waits for is tile t + 1, issued S - 1
 // tiles before.
-template <int MODE, class C>
+//
+// K ranges (calls of up to kFewRows rows).  blockIdx.z runs GR neighbouring ranges of a.kr tiles, each
+// summed from zero, and adds them as part_sum does; GEMM_PARTIAL writes that sum to a.part.
+template <int MODE, class C, int GR>
 __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(GemmArgs a) {
     constexpr int MB = C::MB, NB = C::NB, S = C::S, TK = C::TK, STEPS = C::STEPS;
     constexpr int AI = C::AI, WI = C::WI, D = C::D;
@@ -235,8 +250,13 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(GemmArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const int wm = wave / C::WN, wn = wave % C::WN;
-    const int m0 = blockIdx.x * C::TM, n0 = blockIdx.y * C::TN;
-    const int M = a.M, N = a.N, K = a.K, nk = K / TK;
+    const int cols = C::ONE ? a.cols : C::TN;   // of the tile's TN columns, those that are this workgroup's
+    const int m0 = blockIdx.x * C::TM, n0 = blockIdx.y * cols;
+    const int M = a.M, K = a.K;
+    // this workgroup's k tiles: t0 .. t0 + nk - 1
+    const int kr = a.kr * (64 / TK);
+    const int t0 = MODE == GEMM_PARTIAL ? blockIdx.z * GR * kr : 0;
+    const int nk = MODE == GEMM_PARTIAL ? min(GR * kr, K / TK - t0) : K / TK;
 
     // Copies of this wavefront: uniform bases that advance with the tile, and a 32-bit byte offset
     // per lane.  Activation copy q = wave * AI + i: 8 rows of sub-tile q / (TM / 8); weight copy q =
@@ -244,10 +264,16 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(GemmArgs a) {
     // SWIGLU: the weight tile's rows alternate between Wg and Wu rows n0 / 2 .., 32 of each at a
     // time (16 with one 32-wide block per wavefront, so that each block holds its own pairs).
     constexpr int HALF = NB % 2 == 0 ? 32 : 16;
-    const char *const base_a = reinterpret_cast<const char *>(a.a + (size_t)m0 * a.lda);
+    const char *const base_a = reinterpret_cast<const char *>(a.a + (size_t)m0 * a.lda + (size_t)t0 * (2 * TK));
     const int nrow0 = MODE == GEMM_SWIGLU ? n0 / 2 : n0;
-    const char *const base_w =
-        reinterpret_cast<const char *>(a.w[MODE == GEMM_SWIGLU ? 0 : blockIdx.z] + (size_t)nrow0 * K);
+    const int N = min(a.N, nrow0 + (MODE == GEMM_SWIGLU ? cols / 2 : cols));   // end of this workgroup's columns
+    // SWIGLU of few rows: the groups of kTurn rows of Wg and Wu start their k loops at different tiles.
+    // In step, every workgroup would read the same 128-byte columns of rows a power of two apart, which
+    // crowds some memory channels (64 rows of the 8B-shaped layer, with non-temporal weight copies and
+    // 112 columns per workgroup: 59 -> 49 us; a bare copy loop 48.6 -> 42.2 us from this alone).
+    const int turn = MODE == GEMM_SWIGLU && M <= kFewRows && K % 64 == 0
+                         ? (int)((long)(nrow0 / kTurn) * (K / 64) / ((a.N + kTurn - 1) / kTurn)) * (64 / TK) : 0;
+    const char *const base_w = reinterpret_cast<const char *>(a.w[0] + (size_t)nrow0 * K + (size_t)t0 * TK);
     const long up = MODE == GEMM_SWIGLU ? reinterpret_cast<const char *>(a.w[1]) - reinterpret_cast<const char *>(a.w[0]) : 0;
     uint32_t off_a[AI], off_w[WI];
 #pragma unroll
@@ -268,22 +294,39 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(GemmArgs a) {
     }
     // copy d of tile t into stage st
     auto copy = [&](int t, int st, int d) {
+        if constexpr (MODE == GEMM_SWIGLU) t = t + turn >= nk ? t + turn - nk : t + turn;
         if (d < AI)
             dma16(off_a[d], base_a + (size_t)t * (TK * 4), lds_base + st * C::STAGE + (wave * AI + d) * 1024);
         else
-            dma16(off_w[d - AI], base_w + mat[d - AI] + (size_t)t * (TK * 2),
+            dma16<C::ONE>(off_w[d - AI], base_w + mat[d - AI] + (size_t)t * (TK * 2),
                   lds_base + st * C::STAGE + C::A_BYTES + (wave * WI + d - AI) * 1024);
     };
     // the copies of one tile are issued in STEPS shares
     constexpr auto share = [](int s) { return s * D / STEPS; };
 
-    f32x16 acc[MB][NB];
+    struct Acc {
+        f32x16 v[MB][NB];
+    };
+    Acc sum, tot;   // the running range; GR > 1: the sum of those before it
+    auto &acc = sum.v;
+    auto clear = [](Acc &x) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+            for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+                for (int r = 0; r < 16; ++r) x.v[i][j][r] = 0.f;
+    };
+    auto add = [](Acc &x, const Acc &y) {   // x += y
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) x.v[i][j][r] += y.v[i][j][r];
+    };
+    clear(sum);
+    if (GR > 1) clear(tot);
 
     // byte offsets of this lane's fragments in a stage, without the block and the sub-tile
     const int fr = lane & 31, fk = lane >> 5;   // fragment row and k half of this lane
@@ -390,8 +433,16 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(GemmArgs a) {
         lds_barrier();
         first_frags();
         int t = 0;
-        for (; t < nk - S; ++t) tile(t, yes, yes, integral_constant<int, S - 2>{});
+        // (a loop, not unrolled: with a copy of the body per range the compiler spills the sums)
+#pragma unroll 1
+        for (int end = kr; GR > 1 && end < GR * kr; end += kr) {
+            for (; t < end; ++t) tile(t, yes, yes, integral_constant<int, S - 2>{});
+            add(tot, sum);
+            clear(sum);
+        }
+        for (; t < nk - S; ++t) tile(t, yes, yes, integral_constant<int, S - 2>{});   // (the last range has at least S tiles)
         tail(tail, t, zero);
+        if (GR > 1) add(sum, tot);
     } else {   // fewer tiles than stages: all copied at once
         for (int u = 0; u < nk; ++u)
 #pragma unroll
@@ -432,15 +483,29 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_kernel(GemmArgs a) {
         }
         return;
     }
-    const int col_off = a.out_col[blockIdx.z];
+    if (MODE == GEMM_PARTIAL) {
+        a.out = a.part + (size_t)blockIdx.z * M * a.N;
+        a.ldo = a.N;
+    }
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const int n = n0 + 32 * (wn * NB + j) + (lane & 31);
             if (n >= N) continue;
-            store_block<MODE>(a, acc[i][j], m0 + 32 * (wm * MB + i), M, col_off + n, lane);
+            store_block<MODE>(a, acc[i][j], m0 + 32 * (wm * MB + i), M, n, lane);
         }
+}
+
+// out = res + the sum of SP partial products, [SP][rows][n] with n % 4 == 0, four columns per thread.
+template <int SP>
+__global__ __launch_bounds__(256) void part_residual_kernel(GemmArgs a) {
+    const size_t quads = (size_t)a.M * a.N / 4;
+    for (size_t q = blockIdx.x * 256ull + threadIdx.x; q < quads; q += (size_t)gridDim.x * 256) {
+        const size_t o = 4 * q / a.N * a.ldo + 4 * q % a.N;
+        const float4 r = *reinterpret_cast<const float4 *>(a.res + o);
+        *reinterpret_cast<float4 *>(a.out + o) = add4(r, part_sum<SP>(a.part + 4 * q, (size_t)a.M * a.N));
+    }
 }
 
 // y = x / sqrt(mean(x^2) + eps) * g, written as a pair (row stride ld).  One workgroup per row.
@@ -545,45 +610,177 @@ int grid_for(size_t count) {
 }
 
 using Tile256 = Tile<2, 2, 4, 4, 32, 3>;      // 256 x 256
+using TileWide = Tile<2, 2, 2, 4, 32, 3>;     // 128 x 256
 using Tile128 = Tile<2, 2, 2, 2, 64, 3>;      // 128 x 128
 using Tile128K32 = Tile<2, 2, 2, 2, 32, 3>;   // 128 x 128, K an odd multiple of 32
+using Tile64 = Tile<2, 2, 1, 2, 64, 3, true>;   // 64 x 128
+using Tile32 = Tile<1, 4, 1, 1, 64, 3, true>;   // 32 x 128
 
-template <int MODE>
-void launch_gemm_mode(const GemmArgs &a, int n_mats, hipStream_t st) {
-    // SWIGLU tiles span the rows of both matrices: 2N virtual rows, one grid layer
-    const int nv = MODE == GEMM_SWIGLU ? 2 * a.N : a.N;
-    dim3 grid((a.M + BM - 1) / BM, (nv + BN - 1) / BN, n_mats);
-    dim3 wide((a.M + 255) / 256, (nv + 255) / 256, n_mats);
-    if constexpr (MODE != GEMM_SWIGLU) {
-        if (a.K % BK != 0) {
-            STG_LAUNCH(gemm_kernel<MODE>, grid, dim3(256), 0, st, a);
-            return;
+// How a GEMM runs: K cut into `ranges` ranges of kr tiles of 64, `group` of them at a time in a
+// workgroup; wm x wn tiles.
+struct GemmPlan {
+    int ranges = 1, group = 1, kr = 0, wm = 0, wn = 0;
+    int parts() const { return ranges / group; }
+};
+
+// Cut of K, calls of up to kFewRows rows.  Few rows are bound by the weights, and a [N, K] matrix has
+// only N / 128 workgroups to read them, so K is cut into as many ranges as leave about one workgroup
+// per compute unit, at least 512 deep; fixed by the matrix (see kFewRows).
+// 37 rows of the 8B-shaped layer, whole K -> cut, with the pass that adds the parts: down (32
+// workgroups -> 256) 204 -> 25 us, O 63 -> 11, QKV 62 -> 18.
+//
+// Tiles and grouping, more than 64 rows: the least estimated time, from the rounds of workgroups over
+// the compute units, the time of a workgroup's 64 k at each tile shape with the chip full (us,
+// measured: 256 x 256 2.86, 128 x 256 1.6, 128 x 128 0.88), and the bytes of the partial products
+// (written and read back at about 5 TB/s, and a launch to add them).  Before, 256 x 256 wherever that
+// gave a workgroup per compute unit, else 128 x 128, with whole K: 1200 rows of the 13B-shaped layer
+// gate/up 769 -> 634 us (540 workgroups, 2.1 rounds -> 2160, 8.4), QKV 473 -> 337; 500 rows of the
+// 32B-shaped one down 329 -> 271 us (160 workgroups -> 640 of a quarter of K), QKV 136 -> 113 with
+// what follows it.
+// None of it changes a bit: every tile shape runs the same MFMAs in the same order, and the ranges are
+// added in one order however they are grouped.
+GemmPlan gemm_plan(int M, int N, int K, bool swiglu, bool cut, size_t cap64) {
+    GemmPlan p;
+    const int cus = device_compute_units(), nv = swiglu ? 2 * N : N, tiles = K / 64;
+    if (cut && !swiglu && M <= kFewRows && K % 64 == 0 && N % 4 == 0)
+        for (int r : {8, 4, 3, 2}) {
+            const int kr = (tiles + r - 1) / r, last = tiles - (r - 1) * kr;
+            if ((long)((N + 127) / 128) * r > cus + cus / 16 || kr < 8 || last < 4 || (size_t)r * 64 * N > cap64) continue;
+            p.ranges = r;
+            p.kr = kr;
+            break;
+        }
+    if (M <= 64 && K % 64 == 0) {
+        p.wm = M <= 32 ? 32 : 64;
+        // 112 of a tile's 128 columns where that evens out the last round of workgroups
+        auto rounds = [&](int tn) { return ((nv + tn - 1) / tn * p.ranges + cus - 1) / cus * tn; };
+        p.wn = rounds(112) < rounds(128) ? 112 : 128;
+        return p;
+    }
+    static const struct { int wm, wn; double us; } shapes[] = {{256, 256, 2.86}, {128, 256, 1.6}, {128, 128, 0.88}};
+    double best = 0;
+    for (const auto &t : shapes)
+        for (int g : {4, 3, 2, 1}) {
+            if ((g > 1 && g != std::min(p.ranges, 4)) || (t.wm == 256 && p.ranges > 1)) continue;
+            if (K % 64 != 0 && t.wm != t.wn) continue;
+            const int parts = p.ranges / g;
+            const long wgs = (long)((M + t.wm - 1) / t.wm) * ((nv + t.wn - 1) / t.wn) * parts;
+            double us = (double)((wgs + cus - 1) / cus) * tiles / parts * t.us;
+            if (parts > 1) us += 3 + 8e-6 * parts * M * N / 5;
+            if (best > 0 && us >= best) continue;
+            best = us;
+            p.group = g;
+            p.wm = t.wm;
+            p.wn = t.wn;
+        }
+    return p;
+}
+
+template <int MODE, class C, int GR>
+void launch_shape(GemmArgs a, const GemmPlan &p, hipStream_t st) {
+    const int nv = MODE == GEMM_SWIGLU ? 2 * a.N : a.N;   // SWIGLU tiles span the rows of both matrices
+    a.kr = p.kr;
+    a.cols = p.wn;
+    const dim3 grid((a.M + C::TM - 1) / C::TM, (nv + a.cols - 1) / a.cols, p.parts());
+    STG_LAUNCH((gemm_tile_kernel<MODE, C, GR>), grid, dim3(256), 0, st, a);
+}
+
+template <int MODE, int GR>
+void launch_tile(const GemmArgs &a, const GemmPlan &p, hipStream_t st) {
+    if constexpr (GR == 1) {
+        if (p.wm == 32) return launch_shape<MODE, Tile32, 1>(a, p, st);
+        if (p.wm == 64) return launch_shape<MODE, Tile64, 1>(a, p, st);
+        if constexpr (MODE != GEMM_PARTIAL) {
+            if (p.wm == 256) return launch_shape<MODE, Tile256, 1>(a, p, st);
+            if (a.K % 64 != 0) return launch_shape<MODE, Tile128K32, 1>(a, p, st);
         }
     }
-    // the wide tiles when they still fill every compute unit
-    if ((long)wide.x * wide.y * wide.z >= device_compute_units())
-        STG_LAUNCH((gemm_tile_kernel<MODE, Tile256>), wide, dim3(256), 0, st, a);
-    else if (a.K % 64 == 0)
-        STG_LAUNCH((gemm_tile_kernel<MODE, Tile128>), grid, dim3(256), 0, st, a);
-    else
-        STG_LAUNCH((gemm_tile_kernel<MODE, Tile128K32>), grid, dim3(256), 0, st, a);
+    if constexpr (MODE != GEMM_SWIGLU || GR == 1) {
+        if (p.wn == 256) launch_shape<MODE, TileWide, GR>(a, p, st);
+        else launch_shape<MODE, Tile128, GR>(a, p, st);
+    }
+}
+
+// One part: MODE's own epilogue; several: GEMM_PARTIAL.
+template <int MODE>
+void launch_plan(const GemmArgs &a, const GemmPlan &p, hipStream_t st) {
+    auto go = [&](auto mode) {
+        constexpr int X = decltype(mode)::value;
+        switch (p.group) {
+            case 2: launch_tile<X, 2>(a, p, st); break;
+            case 3: launch_tile<X, 3>(a, p, st); break;
+            case 4: launch_tile<X, 4>(a, p, st); break;
+            default: launch_tile<X, 1>(a, p, st);
+        }
+    };
+    if (p.parts() > 1) go(std::integral_constant<int, GEMM_PARTIAL>{});
+    else go(std::integral_constant<int, MODE>{});
+}
+
+template <int MODE>
+void launch_any_k(const GemmArgs &a, int n_mats, hipStream_t st) {
+    const dim3 grid((a.M + BM - 1) / BM, (a.N + BN - 1) / BN, n_mats);
+    STG_LAUNCH(gemm_kernel<MODE>, grid, dim3(256), 0, st, a);
+}
+
+template <int SP>
+void launch_part_residual(const GemmArgs &a, hipStream_t st) {
+    STG_LAUNCH(part_residual_kernel<SP>, dim3(grid_for((size_t)a.M * a.N / 4)), dim3(256), 0, st, a);
 }
 
 }  // namespace
 
+size_t gemm_part_floats(int rows, int N, int K, size_t cap64) {
+    size_t most = 0;
+    for (int m = 1; m <= min(rows, kFewRows); ++m) {
+        const int parts = gemm_plan(m, N, K, false, true, cap64).parts();
+        if (parts > 1) most = max(most, (size_t)parts * m * N);
+    }
+    return most;
+}
+
 hipError_t launch_gemm(int mode, const GemmArgs &a, int n_mats, hipStream_t st) {
     if (a.M <= 0) return hipSuccess;
-    // every variant runs the same MFMAs in the same order: the choice never changes a bit
+    // variants without a K cut run the same MFMAs in the same order: which of them runs never changes a bit
     if (a.lda < pair_ld(a.K)) return hipErrorInvalidValue;
     if (mode == GEMM_SWIGLU) {
         if (a.K % BK != 0 || n_mats != 1 || !a.out_pair || a.ldo < pair_ld(a.N)) return hipErrorInvalidValue;
-        launch_gemm_mode<GEMM_SWIGLU>(a, 1, st);
+        launch_plan<GEMM_SWIGLU>(a, gemm_plan(a.M, a.N, a.K, true, false, 0), st);
+    } else if (a.K % BK != 0) {
+        if (mode == GEMM_RESIDUAL) launch_any_k<GEMM_RESIDUAL>(a, n_mats, st);
+        else launch_any_k<GEMM_STORE>(a, n_mats, st);
+    } else if (n_mats != 1 || a.out_col[0] != 0) {
+        return hipErrorInvalidValue;
     } else if (mode == GEMM_RESIDUAL) {
-        launch_gemm_mode<GEMM_RESIDUAL>(a, n_mats, st);
+        const GemmPlan p = gemm_plan(a.M, a.N, a.K, false, a.part != nullptr, a.part_cap64);
+        launch_plan<GEMM_RESIDUAL>(a, p, st);
+        switch (p.parts()) {
+            case 2: launch_part_residual<2>(a, st); break;
+            case 3: launch_part_residual<3>(a, st); break;
+            case 4: launch_part_residual<4>(a, st); break;
+            case 8: launch_part_residual<8>(a, st); break;
+        }
     } else {
-        launch_gemm_mode<GEMM_STORE>(a, n_mats, st);
+        launch_plan<GEMM_STORE>(a, gemm_plan(a.M, a.N, a.K, false, false, 0), st);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_qkv(const GemmArgs &g, RopeKvArgs r, hipStream_t st) {
+    if (g.M <= 0) return hipSuccess;
+    r.n_part = 1;
+    r.qkv = g.out;
+    if (g.K % BK != 0) {
+        const hipError_t e = launch_gemm(GEMM_STORE, g, 1, st);
+        if (e != hipSuccess) return e;
+    } else {
+        if (g.lda < pair_ld(g.K)) return hipErrorInvalidValue;
+        const GemmPlan p = gemm_plan(g.M, g.N, g.K, false, g.part != nullptr, g.part_cap64);
+        r.n_part = p.parts();
+        if (r.n_part > 1) r.qkv = g.part;
+        launch_plan<GEMM_STORE>(g, p, st);
+    }
+    return launch_rope_kv_store(r, st);
 }
 
 hipError_t launch_rmsnorm_split(const float *x, const uint16_t *g, float eps, int rows, int H, uint16_t *pair,

@@ -84,7 +84,7 @@ int device_compute_units();
 hipError_t launch_gemv(int mode, GemvArgs a, hipStream_t st, hipEvent_t ev_start = nullptr,
                        hipEvent_t ev_stop = nullptr);
 
-enum GemmMode { GEMM_STORE = 0, GEMM_RESIDUAL = 1, GEMM_SWIGLU = 2 };
+enum GemmMode { GEMM_STORE = 0, GEMM_RESIDUAL = 1, GEMM_SWIGLU = 2, GEMM_PARTIAL = 3 /* internal */ };
 
 // A prefill GEMM operand is an fp32 matrix X [M, K] held as the exact-sum pair X = hi + lo of two
 // bf16 matrices, interleaved by 32-wide k blocks: row m holds, for each block b, the 32 hi values
@@ -107,8 +107,22 @@ struct GemmArgs {
     int out_col[2];               // output column offset of each matrix
     int M, N, K;
     uint16_t *out_pair;           // SWIGLU output pair (row stride ldo >= pair_ld(N))
+    // Calls of up to kFewRows rows cut K into ranges (GemmPlan) whose partial products go here:
+    // gemm_part_floats floats.  Without it K stays whole.
+    float *part;
+    size_t part_cap64;            // floats that calls of up to 64 rows may use of it
+    int kr;                       // (set by the launch) k tiles per range
+    int cols;                     // (set by the launch) columns per workgroup of the tiles for up to 64 rows
 };
 hipError_t launch_gemm(int mode, const GemmArgs &a, int n_mats, hipStream_t st);
+
+// Rows up to which K is cut into ranges.  The cut depends on the matrix only, not on the rows, and
+// the partial products are always added in the same order, so a row's result is the same for any
+// number of rows up to kFewRows (and the same for any number beyond, where K is whole).
+constexpr int kFewRows = 1024;
+// Floats of GemmArgs::part that no call of up to `rows` rows exceeds for a matrix [N, K], and the
+// most that the cut assumes for up to 64 rows (it takes fewer ranges where they would not fit).
+size_t gemm_part_floats(int rows, int N, int K, size_t cap64);
 // y = rmsnorm(x) * g as a pair [rows, H] (row stride ld).
 hipError_t launch_rmsnorm_split(const float *x, const uint16_t *g, float eps, int rows, int H, uint16_t *pair,
                                 long ld, hipStream_t st);
@@ -118,7 +132,8 @@ hipError_t launch_split(const float *x, int rows, int n, uint16_t *pair, long ld
 hipError_t launch_swiglu_split(const float *gu, int F, int rows, uint16_t *pair, long ld, hipStream_t st);
 
 struct RopeKvArgs {
-    const float *qkv;  // [rows, (Hq + 2 Hkv) d]: q heads, then k heads, then v heads
+    const float *qkv;  // [rows, (Hq + 2 Hkv) d]: q heads, then k heads, then v heads; or the partial
+    int n_part;        // products of n_part k ranges, [n_part][rows][...], added here (1: the product)
     float *q_out;      // [rows, Hq d] rotated queries
     const float *cos_t, *sin_t;  // [max_context, d/2]
     KvView kv;
@@ -128,12 +143,15 @@ struct RopeKvArgs {
     const CallMeta *meta; // device copy of the call's row metadata
 };
 hipError_t launch_rope_kv_store(const RopeKvArgs &a, hipStream_t st);
+// The QKV projection and what follows it (r.qkv and r.n_part are set here): g.out is where an uncut
+// product goes.
+hipError_t launch_qkv(const GemmArgs &g, RopeKvArgs r, hipStream_t st);
 
 struct AttnArgs {
     const float *q;      // [rows, Hq d] rotated
     float *out;          // [rows, Hq d]
-    // prefill with the bf16 cache: when set, the output goes here instead of `out`, as the hi/lo
-    // pair the O projection GEMM reads ([rows, out_pair_ld], pair_at layout)
+    // when set, the output goes here instead of `out`, as the hi/lo pair the O projection GEMM reads
+    // ([rows, out_pair_ld], pair_at layout); not for the prefill with an fp32 cache
     uint16_t *out_pair;
     long out_pair_ld;
     float *part_o;       // [rows, Hq, max_splits, d] unnormalised partial outputs

@@ -151,7 +151,7 @@ struct stage {
     size_t part_rows = 0;
     int max_splits = 0;
     float *ws_part_o = nullptr, *ws_part_ml = nullptr;
-    float *ws_split = nullptr, *ws_split_ss = nullptr;  // split matrix-core GEMV partials
+    float *ws_split = nullptr, *ws_split_ss = nullptr;  // partial products of projections cut in K
     void *ws_dense = nullptr;
     size_t ws_dense_bytes = 0;
 
@@ -492,6 +492,20 @@ int set_residency(stage *s, int layer, int code) {
     return STAGE_OK;
 }
 
+// Floats of the partial products of a call's projections: the decode GEMVs' (and what a GEMM of up
+// to 64 rows may use of them), and with them those of the GEMMs of up to kFewRows rows.
+size_t gemv_part_floats(const stage *s) {
+    return (size_t)kGemvMaxSplits * 2 * 16 * std::max<size_t>(std::max<size_t>(s->qkv_rows / 2, s->H), s->F);
+}
+size_t part_floats(const stage *s) {
+    const size_t cap = gemv_part_floats(s);
+    const int qd = s->Hq * s->D;
+    size_t n = cap;
+    for (const auto &[N, K] : {std::pair{s->qkv_rows, s->H}, {s->H, qd}, {s->H, s->F}})
+        n = std::max(n, gemm_part_floats(kFewRows, N, K, cap));
+    return n;
+}
+
 int ensure_workspace(stage *s, size_t rows, bool split_attention) {
     const size_t need_part = split_attention ? rows : 0;
     if (rows <= s->ws_rows && need_part <= s->part_rows) return STAGE_OK;
@@ -770,6 +784,19 @@ int mlp_boundary(stage *s, int layer, const LayerWeights &w) {
     return STAGE_OK;
 }
 
+RopeKvArgs rope_args(stage *s, int layer, int rows, const CallMeta *meta) {
+    RopeKvArgs r{};
+    r.q_out = s->ws_q;
+    r.cos_t = s->d_cos;
+    r.sin_t = s->d_sin;
+    r.kv = kv_view(s, layer);
+    r.n_q_heads = s->Hq;
+    r.kv_fp32 = s->cfg.kv_fp32;
+    r.rows = rows;
+    r.meta = meta;
+    return r;
+}
+
 // Prefill (T >= 2): projections on the matrix cores with bf16 hi/lo operand pairs.
 int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int T, const CallMeta *meta,
                       const float *x_src, float *x_dst) {
@@ -783,19 +810,8 @@ int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int 
     q.w[0] = base + s->off_wqkv / 2;
     q.out = s->ws_qkv; q.ldo = s->qkv_rows;
     q.M = rows; q.N = s->qkv_rows; q.K = H;
-    HIP_TRY(launch_gemm(GEMM_STORE, q, 1, s->cs));
-
-    RopeKvArgs r{};
-    r.qkv = s->ws_qkv;
-    r.q_out = s->ws_q;
-    r.cos_t = s->d_cos;
-    r.sin_t = s->d_sin;
-    r.kv = kv_view(s, layer);
-    r.n_q_heads = s->Hq;
-    r.kv_fp32 = s->cfg.kv_fp32;
-    r.rows = rows;
-    r.meta = meta;
-    HIP_TRY(launch_rope_kv_store(r, s->cs));
+    q.part = s->ws_split; q.part_cap64 = gemv_part_floats(s);
+    HIP_TRY(launch_qkv(q, rope_args(s, layer, rows, meta), s->cs));
 
     AttnArgs at{};
     at.q = s->ws_q;
@@ -820,6 +836,7 @@ int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int 
     o.w[0] = base + s->off_wo / 2;
     o.out = x_dst; o.res = x_src; o.ldo = H;
     o.M = rows; o.N = H; o.K = qd;
+    o.part = s->ws_split; o.part_cap64 = gemv_part_floats(s);
     HIP_TRY(launch_gemm(GEMM_RESIDUAL, o, 1, s->cs));
 
     base = w.mlp;
@@ -851,6 +868,88 @@ int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int 
     dn.w[0] = base + s->off_wd / 2;
     dn.out = x_dst; dn.res = x_dst; dn.ldo = H;
     dn.M = rows; dn.N = H; dn.K = F;
+    dn.part = s->ws_split; dn.part_cap64 = gemv_part_floats(s);
+    HIP_TRY(launch_gemm(GEMM_RESIDUAL, dn, 1, s->cs));
+    return STAGE_OK;
+}
+
+AttnArgs decode_attn_args(stage *s, int layer, int rows, const CallMeta *meta, int grid_splits) {
+    AttnArgs at{};
+    at.q = s->ws_q;
+    at.out = s->ws_attn;
+    at.part_o = s->ws_part_o;
+    at.part_ml = s->ws_part_ml;
+    at.kv = kv_view(s, layer);
+    at.n_q_heads = s->Hq;
+    at.kv_fp32 = s->cfg.kv_fp32;
+    at.rows = rows;
+    at.split_keys = kDecodeSplitKeys;
+    at.max_splits = s->max_splits;
+    at.grid_splits = grid_splits;
+    at.n_seqs = rows;        // decode: one row per sequence
+    at.rows_per_seq = 1;
+    at.meta = meta;
+    return at;
+}
+
+// One token for each of more sequences than a decode GEMV takes at once (16): the GEMVs would read
+// the weights again for every 16 rows, so the projections run as GEMMs on operand pairs, which read
+// them once for all rows (up to 64).  Two 8B-shaped layers, 64 rows at about 830 tokens: 953 -> 380 us
+// (a layer's projections 420 -> 125 us).  At 17 rows one pass over each weight replaces two; up to 16
+// the GEMVs stay, which stream the weights faster (6.5 against 5.4 TB/s) and need no pair passes.
+// The pairs take no memory of their own (stage_decode_noalloc has none to give): the normalised
+// input's lies in ws_h and later ws_q, the attention output's in ws_attn, that of the SwiGLU output
+// in ws_h.  The shape has to leave room for that, and whole 64-wide k tiles.
+constexpr int kGemvRows = 16;
+bool decode_by_gemm(const stage *s, int rows) {
+    const int qd = s->Hq * s->D;
+    return rows > kGemvRows && s->H % 64 == 0 && s->F % 64 == 0 && qd % 64 == 0 && s->F >= s->H && qd >= s->H;
+}
+int run_layer_rows(stage *s, int layer, const LayerWeights &w, int rows, const CallMeta *meta, int grid_splits,
+                   const float *x_src, float *x_dst, const TimeRec &rec) {
+    const int H = s->H, F = s->F, qd = s->Hq * s->D;
+    const size_t cap = gemv_part_floats(s);
+    uint16_t *const h = reinterpret_cast<uint16_t *>(s->ws_h), *const att = reinterpret_cast<uint16_t *>(s->ws_attn);
+    uint16_t *const y2 = reinterpret_cast<uint16_t *>(s->ws_q);
+
+    HIP_TRY(launch_rmsnorm_split(x_src, w.mha + s->off_g1 / 2, s->cfg.rms_eps, rows, H, h, pair_ld(H), s->cs));
+    GemmArgs q{};
+    q.a = h; q.lda = pair_ld(H);
+    q.w[0] = w.mha + s->off_wqkv / 2;
+    q.out = s->ws_split; q.ldo = s->qkv_rows;
+    q.M = rows; q.N = s->qkv_rows; q.K = H;
+    q.part = s->ws_split; q.part_cap64 = cap;
+    HIP_TRY(launch_qkv(q, rope_args(s, layer, rows, meta), s->cs));
+    AttnArgs at = decode_attn_args(s, layer, rows, meta, grid_splits);
+    at.out_pair = att;
+    at.out_pair_ld = pair_ld(qd);
+    HIP_TRY(launch_attention(at, s->cs));
+    GemmArgs o{};
+    o.a = att; o.lda = pair_ld(qd);
+    o.w[0] = w.mha + s->off_wo / 2;
+    o.out = x_dst; o.res = x_src; o.ldo = H;
+    o.M = rows; o.N = H; o.K = qd;
+    o.part = s->ws_split; o.part_cap64 = cap;
+    HIP_TRY(launch_gemm(GEMM_RESIDUAL, o, 1, s->cs));
+
+    int rc = mlp_boundary(s, layer, w);
+    if (rc) return rc;
+    HIP_TRY(launch_rmsnorm_split(x_dst, w.mlp + s->off_g2 / 2, s->cfg.rms_eps, rows, H, y2, pair_ld(H), s->cs));
+    GemmArgs gu{};
+    gu.a = y2; gu.lda = pair_ld(H);
+    gu.w[0] = w.mlp + s->off_wg / 2;
+    gu.w[1] = w.mlp + s->off_wu / 2;
+    gu.M = rows; gu.N = F; gu.K = H;
+    gu.out_pair = h; gu.ldo = pair_ld(F);
+    if (rec.a) HIP_TRY(hipEventRecord(rec.a, s->cs));
+    HIP_TRY(launch_gemm(GEMM_SWIGLU, gu, 1, s->cs));
+    if (rec.b) HIP_TRY(hipEventRecord(rec.b, s->cs));
+    GemmArgs dn{};
+    dn.a = h; dn.lda = pair_ld(F);
+    dn.w[0] = w.mlp + s->off_wd / 2;
+    dn.out = x_dst; dn.res = x_dst; dn.ldo = H;
+    dn.M = rows; dn.N = H; dn.K = F;
+    dn.part = s->ws_split; dn.part_cap64 = cap;
     HIP_TRY(launch_gemm(GEMM_RESIDUAL, dn, 1, s->cs));
     return STAGE_OK;
 }
@@ -860,6 +959,19 @@ int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int 
     if (T >= 2) return run_layer_prefill(s, layer, w, rows, T, meta, x_src, x_dst);
     if ((size_t)rows > s->part_rows || !s->ws_part_o || !s->ws_part_ml)
         return s->fail(STAGE_ESTATE, "attention partials sized for %zu rows, call has %d", s->part_rows, rows);
+    // Timed kernel: the gate/up projection of one layer per call (rotating), so that the events
+    // barely perturb the step.
+    TimeRec rec{2, layer, nullptr, nullptr};
+    if ((s->cfg.timing & STAGE_TIME_GATEUP) && layer == (int)((s->calls - 1) % s->L)) {
+        rec.a = pooled_event(s);
+        rec.b = pooled_event(s);
+        if (!rec.a || !rec.b) return s->fail(STAGE_EHIP, "hipEventCreate failed");
+    }
+    if (decode_by_gemm(s, rows)) {
+        const int rc = run_layer_rows(s, layer, w, rows, meta, grid_splits, x_src, x_dst, rec);
+        if (rc == STAGE_OK && rec.a) s->recs.push_back(rec);
+        return rc;
+    }
     const uint16_t *base = w.mha, *mlp = w.mlp;
     const size_t qd = (size_t)s->Hq * s->D;
 
@@ -883,21 +995,7 @@ int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int 
     q.split_part = s->ws_split;  // matrix-core launches may split K
     q.split_ss = s->ws_split_ss;
 
-    AttnArgs at{};
-    at.q = s->ws_q;
-    at.out = s->ws_attn;
-    at.part_o = s->ws_part_o;
-    at.part_ml = s->ws_part_ml;
-    at.kv = kv_view(s, layer);
-    at.n_q_heads = s->Hq;
-    at.kv_fp32 = s->cfg.kv_fp32;
-    at.rows = rows;
-    at.split_keys = kDecodeSplitKeys;
-    at.max_splits = s->max_splits;
-    at.grid_splits = grid_splits;
-    at.n_seqs = rows;        // decode: one row per sequence
-    at.rows_per_seq = 1;
-    at.meta = meta;
+    const AttnArgs at = decode_attn_args(s, layer, rows, meta, grid_splits);
 
     GemvArgs o{};
     o.w = base + s->off_wo / 2;
@@ -940,14 +1038,6 @@ int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int 
     dn.split_part = s->ws_split;
     dn.split_ss = s->ws_split_ss;
 
-    // Timed kernel: the gate/up projection of one layer per call (rotating), so that the events
-    // barely perturb the step.
-    TimeRec rec{2, layer, nullptr, nullptr};
-    if ((s->cfg.timing & STAGE_TIME_GATEUP) && layer == (int)((s->calls - 1) % s->L)) {
-        rec.a = pooled_event(s);
-        rec.b = pooled_event(s);
-        if (!rec.a || !rec.b) return s->fail(STAGE_EHIP, "hipEventCreate failed");
-    }
     HIP_TRY(launch_gemv(GEMV_NORM_ROPE_KV, q, s->cs));
     HIP_TRY(launch_attention(at, s->cs));
     HIP_TRY(launch_gemv(GEMV_PLAIN_RESIDUAL, o, s->cs));
@@ -1210,8 +1300,7 @@ ScratchLayout scratch_layout(const stage *s, size_t rows, int splits) {
     p.part_ml = take(rows * s->Hq * (size_t)splits * 2 * sizeof(float));
     p.has_split = rows >= 3;
     if (p.has_split) {
-        const size_t units = std::max<size_t>(std::max<size_t>(s->qkv_rows / 2, s->H), s->F);
-        p.split = take(sizeof(float) * kGemvMaxSplits * 2 * 16 * units);
+        p.split = take(sizeof(float) * gemv_part_floats(s));
         p.split_ss = take(sizeof(float) * kGemvMaxSplits * 16);
     }
     p.total = off;
@@ -1331,8 +1420,7 @@ int stage_init(const stage_config *cfg, stage **out) {
         hipMalloc(&s->d_cos, sizeof(float) * (size_t)c.max_context * (s->D / 2)) != hipSuccess ||
         hipMalloc(&s->d_sin, sizeof(float) * (size_t)c.max_context * (s->D / 2)) != hipSuccess ||
         hipMalloc(&s->d_meta, sizeof(CallMeta)) != hipSuccess ||
-        hipMalloc(&s->ws_split, sizeof(float) * kGemvMaxSplits * 2 * 16 *
-                                    std::max<size_t>(std::max<size_t>(s->qkv_rows / 2, s->H), s->F)) != hipSuccess ||
+        hipMalloc(&s->ws_split, sizeof(float) * part_floats(s)) != hipSuccess ||
         hipMalloc(&s->ws_split_ss, sizeof(float) * kGemvMaxSplits * 16) != hipSuccess) {
         (void)hipGetLastError();
         return cleanup(STAGE_ENOMEM);
@@ -1348,8 +1436,7 @@ int stage_init(const stage_config *cfg, stage **out) {
             else if (create_private_stream(c.device, &ln.cs) == hipSuccess) ln.own_cs = true;
             else return cleanup(STAGE_EHIP);
             if (hipMalloc(&ln.d_meta, sizeof(CallMeta)) != hipSuccess ||
-                hipMalloc(&ln.ws_split, sizeof(float) * kGemvMaxSplits * 2 * 16 *
-                                            std::max<size_t>(std::max<size_t>(s->qkv_rows / 2, s->H), s->F)) != hipSuccess ||
+                hipMalloc(&ln.ws_split, sizeof(float) * part_floats(s)) != hipSuccess ||
                 hipMalloc(&ln.ws_split_ss, sizeof(float) * kGemvMaxSplits * 16) != hipSuccess) {
                 (void)hipGetLastError();
                 return cleanup(STAGE_ENOMEM);
