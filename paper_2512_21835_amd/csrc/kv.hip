@@ -91,6 +91,7 @@ __global__ void table_write_kernel(TableChunk c) {
     if (i < c.n) c.table[c.idx[i]] = c.val[i];
 }
 
+// The general form, one element at a time: dense buffers off 16-byte boundaries.
 template <typename T>
 __global__ __launch_bounds__(256) void kv_copy_kernel(KvCopyArgs a) {
     const int t = blockIdx.x, layer = blockIdx.y;
@@ -112,6 +113,46 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(KvCopyArgs a) {
         } else {
             dk[dbase + i] = pool[pk];
             dv[dbase + i] = pool[pv];
+        }
+    }
+}
+
+// 16-byte chunks, kCopyDeep of K and of V in flight per thread; a head vector is 2^row_bits chunks,
+// contiguous on both sides.  Bound by its bytes once enough of them are in flight: 500 tokens of 16
+// 70B-shaped layers (32.8 MB read, 32.8 MB written per direction) 19.4 us with an element per access ->
+// 10.8 us (6.1 TB/s).
+constexpr int kCopyDeep = 4;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // (arrays of the uint4 struct would not stay in registers)
+template <bool TO_POOL>
+__global__ __launch_bounds__(256) void kv_copy_wide_kernel(KvCopyArgs a, int row_bits, uint32_t chunks) {
+    const int layer = blockIdx.y, hkv = a.n_kv_heads;
+    u32x4 *const pool = reinterpret_cast<u32x4 *>(static_cast<char *>(a.pool_base) + (size_t)layer * a.layer_stride);
+    const size_t head = (size_t)kBlockTokens << row_bits, dense0 = (size_t)layer * chunks;   // (chunks: of K, per layer)
+    u32x4 *const dk = static_cast<u32x4 *>(a.k) + dense0, *const dv = static_cast<u32x4 *>(a.v) + dense0;
+    const int *const table = a.block_table + (size_t)a.slot * a.max_blocks;
+    const uint32_t c0 = blockIdx.x * (256u * kCopyDeep) + threadIdx.x;
+    size_t at[kCopyDeep];   // the chunk's place in the pool (K; V is hkv heads further)
+#pragma unroll
+    for (int u = 0; u < kCopyDeep; ++u) {   // chunks past the last: the last one (in bounds, not stored)
+        const uint32_t c = min(c0 + 256u * u, chunks - 1), row = c >> row_bits;
+        const int pos = a.pos0 + (int)(row / hkv), g = (int)(row % hkv);
+        at[u] = ((size_t)table[pos / kBlockTokens] * 2 * hkv + g) * head + ((size_t)(pos % kBlockTokens) << row_bits) +
+                (c & ((1u << row_bits) - 1));
+    }
+    u32x4 k[kCopyDeep], v[kCopyDeep];
+#pragma unroll
+    for (int u = 0; u < kCopyDeep; ++u) {
+        const uint32_t c = min(c0 + 256u * u, chunks - 1);
+        const u32x4 *const pk = TO_POOL ? dk + c : pool + at[u], *const pv = TO_POOL ? dv + c : pool + at[u] + hkv * head;
+        k[u] = *pk;
+        v[u] = *pv;
+    }
+#pragma unroll
+    for (int u = 0; u < kCopyDeep; ++u) {
+        const uint32_t c = c0 + 256u * u;
+        if (c < chunks) {
+            *(TO_POOL ? pool + at[u] : dk + c) = k[u];
+            *(TO_POOL ? pool + at[u] + hkv * head : dv + c) = v[u];
         }
     }
 }
@@ -207,6 +248,19 @@ hipError_t launch_table_write(int *table, const int *idx, const int *val, int n,
 
 hipError_t launch_kv_copy(const KvCopyArgs &a, hipStream_t st) {
     if (a.n <= 0) return hipSuccess;
+    // whole 16-byte chunks where both dense buffers start on such a boundary (a device buffer of the
+    // caller's may not; the pool's head vectors always do) and a layer's chunks count in 31 bits
+    const int row_bytes = a.head_dim * (a.kv_fp32 ? 4 : 2);
+    const size_t chunks = (size_t)a.n * a.n_kv_heads * row_bytes / 16;
+    const bool pow2 = row_bytes >= 16 && (row_bytes & (row_bytes - 1)) == 0;
+    if (pow2 && chunks < (size_t(1) << 31) && ((uintptr_t)a.k | (uintptr_t)a.v) % 16 == 0) {
+        int row_bits = 0;
+        while (16 << row_bits < row_bytes) ++row_bits;
+        const dim3 grid((unsigned)((chunks + 256 * kCopyDeep - 1) / (256 * kCopyDeep)), a.n_layers);
+        if (a.to_pool) STG_LAUNCH(kv_copy_wide_kernel<true>, grid, dim3(256), 0, st, a, row_bits, (uint32_t)chunks);
+        else STG_LAUNCH(kv_copy_wide_kernel<false>, grid, dim3(256), 0, st, a, row_bits, (uint32_t)chunks);
+        return hipGetLastError();
+    }
     dim3 grid(a.n, a.n_layers);
     if (a.kv_fp32)
         STG_LAUNCH(kv_copy_kernel<float>, grid, dim3(256), 0, st, a);
