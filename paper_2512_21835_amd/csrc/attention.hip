@@ -1,15 +1,8 @@
 // Causal grouped-query attention over the paged KV cache, fp32 arithmetic.
 //
-// One workgroup handles one (row, KV head, key split): the G = Hq/Hkv query heads that share the
-// KV head, over a range of keys.  Keys are walked in chunks of 64.  Inside a chunk, 128-bit loads
-// fetch one K row per D/8 lanes (a 16-token block of one head is 4 KiB contiguous in the pool);
-// the lanes of a key reduce their partial dot products with shuffles, scores go to LDS, one
-// wavefront per head takes the chunk maximum and exponentials (online softmax across chunks), and
-// the same lanes then accumulate P.V from V rows fetched the same way.
-//
-// Prefill (split_keys == 0): with a bf16 cache, attn_prefill_mfma runs the products on the matrix
-// cores (flash-attention tiling, below); with an fp32 cache (the parity mode), attn_kernel: one
-// workgroup per (row, KV head) walks all of the row's keys.  Decode (split_keys > 0): the context is
+// Prefill (split_keys == 0): flash-attention tiling on the matrix cores, the G = Hq/Hkv query heads
+// that share a KV head in one workgroup; attn_prefill_mfma with a bf16 cache (operands as bf16 hi/lo
+// pairs), attn_prefill_f32 with an fp32 one.  Decode (split_keys > 0): the context is
 // cut into splits of split_keys keys so that one token's attention still fills the GPU, and a
 // second launch (attn_merge) merges each row's splits.  With a bf16 cache and 128-wide heads the
 // splits run on the matrix cores (attn_decode_mfma: the G query heads of a KV head are the N
@@ -23,6 +16,10 @@
 
 namespace stg {
 namespace {
+
+// 16 bytes in registers (arrays of HIP's uint4 and float4 structs may go to scratch memory)
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kChunk = 64;
 constexpr int kMaxDecodeSplits = 256;  // splits one row may have (max_context / split_keys)
@@ -200,146 +197,6 @@ __device__ __forceinline__ void attn_decode_task(const AttnArgs &a, int split, i
 }
 
 
-template <int G, int D, bool F32KV>
-__global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
-    constexpr int LPK = D / 8;        // lanes per key row
-    constexpr int KPW = 64 / LPK;     // keys per wavefront per step
-    constexpr int KPS = 4 * KPW;      // keys per workgroup per step
-    static_assert(kChunk % KPS == 0, "chunk must be a multiple of keys per step");
-    const int g = blockIdx.y, row = blockIdx.z;
-    const int sidx = row / a.meta->rows_per_seq;
-    const int pos = a.meta->pos0[sidx] + row % a.meta->rows_per_seq;
-    const int slot = a.meta->seq_slot[sidx];
-    const int ctx = pos + 1;
-    const int kbeg = 0, kend = ctx;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int kl = lane / LPK;        // key slot of this lane within the wavefront step
-    const int sub = lane % LPK;
-    const int c0 = sub * 8;
-    const int hq_total = a.n_q_heads;
-    const size_t q_ld = (size_t)hq_total * D;
-    const int hkv = a.kv.n_kv_heads;
-    const int *table = a.kv.block_table + (size_t)slot * a.kv.max_blocks;
-    const size_t blk_stride = (size_t)2 * hkv * kBlockTokens * D;
-
-    __shared__ float s_p[G][kChunk];
-    __shared__ float s_m[G], s_l[G], s_alpha[G];
-    __shared__ float s_o[4][G][D];
-
-    const float scale = 1.f / sqrtf((float)D);
-    float q[G][8];
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-        const float *qp = a.q + row * q_ld + (size_t)(g * G + h) * D + c0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) q[h][j] = qp[j] * scale;
-    }
-    if (tid < G) { s_m[tid] = -INFINITY; s_l[tid] = 0.f; }
-    float o[G][8];
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) o[h][j] = 0.f;
-    __syncthreads();
-
-    for (int kc = kbeg; kc < kend; kc += kChunk) {
-        const int n = min(kChunk, kend - kc);
-        // scores of this chunk
-        for (int base = 0; base < kChunk; base += KPS) {
-            const int kk = base + wave * KPW + kl;
-            float part[G];
-#pragma unroll
-            for (int h = 0; h < G; ++h) part[h] = 0.f;
-            if (kk < n) {
-                const int key = kc + kk;
-                const size_t e = (size_t)table[key / kBlockTokens] * blk_stride +
-                                 ((size_t)g * kBlockTokens + key % kBlockTokens) * D + c0;
-                float kf[8];
-                load8<F32KV>(a.kv.pool, e, kf);
-#pragma unroll
-                for (int h = 0; h < G; ++h)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) part[h] = fmaf(q[h][j], kf[j], part[h]);
-            }
-#pragma unroll
-            for (int h = 0; h < G; ++h)
-#pragma unroll
-                for (int o2 = LPK / 2; o2 >= 1; o2 >>= 1) part[h] += lane_xor(part[h], o2);
-            if (kk < n && sub == 0) {
-#pragma unroll
-                for (int h = 0; h < G; ++h) s_p[h][kk] = part[h];
-            }
-        }
-        __syncthreads();
-        // online softmax update, one wavefront per head
-        for (int h = wave; h < G; h += 4) {
-            const float sv = lane < n ? s_p[h][lane] : -INFINITY;
-            float mx = sv;
-#pragma unroll
-            for (int o2 = 32; o2 >= 1; o2 >>= 1) mx = fmaxf(mx, lane_xor(mx, o2));
-            const float m_old = s_m[h];
-            const float m_new = fmaxf(m_old, mx);
-            const float p = lane < n ? expf(sv - m_new) : 0.f;
-            float sum = p;
-#pragma unroll
-            for (int o2 = 32; o2 >= 1; o2 >>= 1) sum += lane_xor(sum, o2);
-            s_p[h][lane] = p;
-            if (lane == 0) {
-                const float alpha = expf(m_old - m_new);  // 0 on the first chunk (m_old = -inf)
-                s_alpha[h] = alpha;
-                s_l[h] = s_l[h] * alpha + sum;
-                s_m[h] = m_new;
-            }
-        }
-        __syncthreads();
-        // P.V
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            const float al = s_alpha[h];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) o[h][j] *= al;
-        }
-        for (int base = 0; base < kChunk; base += KPS) {
-            const int kk = base + wave * KPW + kl;
-            if (kk < n) {
-                const int key = kc + kk;
-                const size_t e = (size_t)table[key / kBlockTokens] * blk_stride +
-                                 ((size_t)(hkv + g) * kBlockTokens + key % kBlockTokens) * D + c0;
-                float vf[8];
-                load8<F32KV>(a.kv.pool, e, vf);
-#pragma unroll
-                for (int h = 0; h < G; ++h) {
-                    const float p = s_p[h][kk];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) o[h][j] = fmaf(p, vf[j], o[h][j]);
-                }
-            }
-        }
-        __syncthreads();
-    }
-
-    // reduce the key slots: lanes with equal `sub` inside a wavefront, then across wavefronts
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-#pragma unroll
-            for (int o2 = 32; o2 >= LPK; o2 >>= 1) o[h][j] += lane_xor(o[h][j], o2);
-    if (kl == 0) {
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s_o[wave][h][c0 + j] = o[h][j];
-    }
-    __syncthreads();
-    for (int i = tid; i < G * D; i += 256) {
-        const int h = i / D, c = i % D;
-        const float v = ((s_o[0][h][c] + s_o[1][h][c]) + s_o[2][h][c]) + s_o[3][h][c];
-        a.out[row * q_ld + (size_t)(g * G + h) * D + c] = v / s_l[h];
-    }
-}
-
 template <int G, int D, bool F32KV, bool FINAL>
 __global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a) {
     __shared__ DecodeSmem<G, D> sm;
@@ -457,7 +314,6 @@ __device__ __forceinline__ void split8(const float *x, bf16x8_t &hi, bf16x8_t &l
     }
 }
 
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 // Decode attention of one (64-key split, KV head g, row) on the matrix cores (bf16 KV, D = 128,
 // G <= 16): S^T = K Q^T with the K rows of the split's cache blocks as the A operand (one 16-key
 // block per wavefront) and Q as a bf16 hi/lo pair; softmax statistics per head from the MFMA
@@ -825,14 +681,216 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(AttnArgs a) {
         for (int i = 0; i < 16; ++i) orow[32 * b + 8 * (i / 4) + 4 * half + (i % 4)] = o[b][i] * inv;
 }
 
+// Prefill attention over an fp32 cache, in fp32 throughout, on v_mfma_f32_32x32x2_f32 (fp32 operands,
+// products and sums; twice the vector ALUs' rate and none of their operand traffic).  One workgroup: 64
+// query rows = G heads x 64 / G consecutive positions of one sequence, one KV head.  Wavefront w: rows
+// 32 (w % 2) .. + 31 (row r: head r / BQ, position offset r % BQ) over the keys of half w / 2 of each
+// 64-key tile; the two halves' states are merged through LDS at the end (a row's result depends on its
+// position only).  S^T = K Q^T, softmax in-lane, O^T += V^T P^T, where the lane layout of S^T is
+// already the one of P^T's operand.  The k index of an MFMA is 8 u + j for lanes 0..31 and 8 u + 4 + j
+// for the rest, so that operands load 16 bytes at a time.
+// Bound by its MFMAs; 68 KB of LDS leave two workgroups per compute unit, one of which multiplies
+// while the other loads.  2 x 600 tokens of the 13B-shaped stage (40 heads): a workgroup per row and
+// KV head on the vector ALUs 700 us -> 186 us, without the pass that made the O projection's operand pair (9 us).
+template <int G, int D>
+__global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
+    constexpr int KEYS = 64, BQ = 64 / G;
+    constexpr int KROW = D + 4, VROW32 = D + 8;   // row strides (padding: lanes on distinct banks)
+    constexpr int QU = D / 8, NB = D / 32;
+    __shared__ __align__(16) float sk[KEYS * KROW];
+    __shared__ __align__(16) float sv[KEYS * VROW32];
+    static_assert(KEYS * KROW >= 64 * (16 * NB + 2), "a wavefront's state fits where K (V) was");
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wq = wave & 1, kh = wave >> 1;
+    const int qb = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, sidx = blockIdx.y;  // the longest blocks of all first
+    const int T = a.rows_per_seq;
+    const int pos0 = a.meta->pos0[sidx], slot = a.meta->seq_slot[sidx];
+    const int hkv = a.kv.n_kv_heads, hq_total = a.n_q_heads;
+    const size_t q_ld = (size_t)hq_total * D;
+    const int *table = a.kv.block_table + (size_t)slot * a.kv.max_blocks;
+    const float *pool = static_cast<const float *>(a.kv.pool);
+    const size_t blk_stride = (size_t)2 * hkv * kBlockTokens * D;
+
+    // this lane's query (column) and its position
+    const int r = 32 * wq + col, hh = r / BQ, t = qb * BQ + r % BQ;
+    const bool qvalid = t < T;
+    const int qpos = pos0 + (qvalid ? t : T - 1);
+    const size_t qrow = (size_t)sidx * T + (qvalid ? t : T - 1);
+    float q[QU][4];   // d 8 u + 4 half + j, scaled by 1 / sqrt(d)
+    {
+        const float scale = 1.f / sqrtf((float)D);
+        const float *qp = a.q + qrow * q_ld + (size_t)(g * G + hh) * D + 4 * half;
+#pragma unroll
+        for (int u = 0; u < QU; ++u) {
+            const float4 v = *reinterpret_cast<const float4 *>(qp + 8 * u);
+            q[u][0] = v.x * scale;
+            q[u][1] = v.y * scale;
+            q[u][2] = v.z * scale;
+            q[u][3] = v.w * scale;
+        }
+    }
+    f32x16_t o[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+
+    // the last and the first position of the block, the last of this wavefront (keys past it are
+    // masked in every one of its rows)
+    const int block_min = pos0 + qb * BQ, n_keys = pos0 + min(T, (qb + 1) * BQ);
+    const int wave_max = pos0 + min(T, BQ > 32 ? qb * BQ + 32 * wq + 32 : (qb + 1) * BQ) - 1;
+
+    for (int base = 0; base < n_keys; base += KEYS) {
+        __syncthreads();            // the previous tile's LDS reads are done
+        // 64 keys x D of K and of V, 16 bytes per access; keys past the block's last: that one (their
+        // scores are masked).  A row whose mask hides a key must not meet its V, which may hold an
+        // infinity or NaN (0 x inf): a tile that hides keys notes whether any V of it does.
+        constexpr int CH = D / 4, PER = 4;
+        bool odd = false;
+#pragma unroll 1
+        for (int c0 = tid; c0 < KEYS * CH; c0 += 256 * PER) {
+            f32x4_t kr[PER], vr[PER];
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int c = c0 + 256 * i, kp = min(base + c / CH, n_keys - 1);
+                const float *p = pool + (size_t)table[kp / kBlockTokens] * blk_stride +
+                                 ((size_t)g * kBlockTokens + kp % kBlockTokens) * D + c % CH * 4;
+                kr[i] = *reinterpret_cast<const f32x4_t *>(p);
+                vr[i] = *reinterpret_cast<const f32x4_t *>(p + (size_t)hkv * kBlockTokens * D);
+            }
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int c = c0 + 256 * i;
+                *reinterpret_cast<f32x4_t *>(sk + c / CH * KROW + c % CH * 4) = kr[i];
+                *reinterpret_cast<f32x4_t *>(sv + c / CH * VROW32 + c % CH * 4) = vr[i];
+                const float big = fmaxf(fmaxf(fabsf(vr[i].x), fabsf(vr[i].y)), fmaxf(fabsf(vr[i].z), fabsf(vr[i].w)));
+                const float sum = (vr[i].x + vr[i].y) + (vr[i].z + vr[i].w);   // (NaN if any is)
+                odd = odd || !(big < INFINITY) || sum != sum;
+            }
+        }
+        const bool hides = base + KEYS - 1 > block_min;
+        const bool careful = __syncthreads_or(hides && odd);
+        const int k0 = base + 32 * kh;
+        if (k0 > wave_max) continue;           // wave-uniform: every key of this half is masked
+        f32x16_t s, s1;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = s1[i] = 0.f;
+        const float *kp = sk + (32 * kh + col) * KROW + 4 * half;
+#pragma unroll
+        for (int u = 0; u < QU; u += 2) {
+            const float4 x = *reinterpret_cast<const float4 *>(kp + 8 * u), y = *reinterpret_cast<const float4 *>(kp + 8 * u + 8);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, q[u][0], s, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(y.x, q[u + 1][0], s1, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, q[u][1], s, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(y.y, q[u + 1][1], s1, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, q[u][2], s, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(y.z, q[u + 1][2], s1, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, q[u][3], s, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(y.w, q[u + 1][3], s1, 0, 0, 0);
+            if (u % 8 == 6) __builtin_amdgcn_sched_barrier(0);   // (all K reads at once would not fit the registers)
+        }
+        // register i: key k0 + 8 (i / 4) + 4 half + i % 4 of query column col
+        float mt = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            s[i] = k0 + 8 * (i / 4) + 4 * half + i % 4 > qpos ? -INFINITY : s[i] + s1[i];
+            mt = fmaxf(mt, s[i]);
+        }
+        mt = fmaxf(mt, lane_xor(mt, 32));
+        const float m_new = fmaxf(m_run, mt);
+        const float alpha = m_run == -INFINITY ? 0.f : expf(m_run - m_new);
+        float ps = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            s[i] = s[i] == -INFINITY ? 0.f : expf(s[i] - m_new);
+            ps += s[i];
+        }
+        ps += lane_xor(ps, 32);
+        l_run = l_run * alpha + ps;
+        m_run = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {   // some lane's maximum moved
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
+        }
+        if (careful) {   // key by key, hidden keys left out
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float other = lane_xor(s[i], 32);
+#pragma unroll 1
+                for (int e = 0; e < 2; ++e) {
+                    const int key = 8 * (i / 4) + 4 * e + i % 4;
+                    if (k0 + key > qpos) continue;
+                    const float p = e == half ? s[i] : other;
+                    const float *vr = sv + (32 * kh + key) * VROW32 + 4 * half;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) o[b][j] = fmaf(p, vr[32 * b + 8 * (j / 4) + j % 4], o[b][j]);
+                        __builtin_amdgcn_sched_barrier(0);   // (registers)
+                    }
+                }
+            }
+            continue;
+        }
+        const float *vp = sv + (32 * kh + 4 * half) * VROW32 + col;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vp[(8 * (i / 4) + i % 4) * VROW32 + 32 * b], s[i], o[b], 0, 0, 0);
+    }
+
+    // the second key half's state joins the first's (which holds key 0: never empty)
+    __syncthreads();
+    float *const st = (wq ? sv : sk) + lane;
+    if (kh == 1) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) st[64 * (16 * b + i)] = o[b][i];
+        st[64 * 16 * NB] = m_run;
+        st[64 * (16 * NB + 1)] = l_run;
+    }
+    __syncthreads();
+    if (kh == 1 || !qvalid) return;
+    const float m1 = st[64 * 16 * NB], l1 = st[64 * (16 * NB + 1)];
+    const float m = fmaxf(m_run, m1);
+    const bool both = m1 > -INFINITY || l1 != 0.f;   // (l1 is NaN, too, if every score of the half is)
+    const float w0 = expf(m_run - m), w1 = both ? expf(m1 - m) : 0.f;
+    const float l = both ? fmaf(l1, w1, l_run * w0) : l_run * w0;
+    const int k0 = (g * G + hh) * D;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {   // O^T[d = 32 b + 8 j + 4 half + x][query col]
+            float v[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int i = 4 * j + x;
+                v[x] = o[b][i] * w0;
+                if (both) v[x] = fmaf(st[64 * (16 * b + i)], w1, v[x]);
+                v[x] /= l;
+            }
+            const int c = k0 + 32 * b + 8 * j + 4 * half;
+            const float4 v4 = make_float4(v[0], v[1], v[2], v[3]);
+            if (a.out_pair) store_pair4(a.out_pair + qrow * a.out_pair_ld + pair_at(c), v4);
+            else *reinterpret_cast<float4 *>(a.out + qrow * q_ld + c) = v4;
+        }
+}
+
 template <int G, int D>
 hipError_t launch_gd(const AttnArgs &a, hipStream_t st) {
     const int hkv = a.kv.n_kv_heads;
     if (a.split_keys == 0) {
+        if (a.n_seqs * a.rows_per_seq != a.rows) return hipErrorInvalidValue;
         if (a.kv_fp32) {
-            STG_LAUNCH((attn_kernel<G, D, true>), dim3(1, hkv, a.rows), dim3(256), 0, st, a);
+            constexpr int BQ = 64 / G;
+            dim3 grid(hkv, a.n_seqs, (a.rows_per_seq + BQ - 1) / BQ);
+            STG_LAUNCH((attn_prefill_f32<G, D>), grid, dim3(256), 0, st, a);
         } else {
-            if (a.n_seqs * a.rows_per_seq != a.rows) return hipErrorInvalidValue;
             constexpr int BQ = 128 / G;
             dim3 grid((a.rows_per_seq + BQ - 1) / BQ, hkv, a.n_seqs);
             STG_LAUNCH((attn_prefill_mfma<G, D>), grid, dim3(256), 0, st, a);

@@ -578,17 +578,6 @@ __global__ __launch_bounds__(256) void rmsnorm_split_rows_kernel(const float *x,
     }
 }
 
-// The pair (row stride ld) of an fp32 matrix [rows, n] (row stride n, n % 4 == 0), four elements
-// per thread.
-__global__ __launch_bounds__(256) void split_kernel(const float *x, int rows, int n, uint16_t *pair, long ld) {
-    const size_t quads = (size_t)rows * n / 4;
-    for (size_t q = blockIdx.x * 256ull + threadIdx.x; q < quads; q += (size_t)gridDim.x * 256) {
-        const size_t r = 4 * q / n;
-        const int c = (int)(4 * q % n);
-        store_pair4(pair + r * ld + pair_at(c), *reinterpret_cast<const float4 *>(x + 4 * q));
-    }
-}
-
 // h = silu(gate) * up from gu [rows, 2F] (gate columns first), written as a pair [rows, F] (row
 // stride ld; F % 4 == 0), four elements per thread.
 __global__ __launch_bounds__(256) void swiglu_split_kernel(const float *gu, int F, int rows, uint16_t *pair,
@@ -792,14 +781,6 @@ hipError_t launch_rmsnorm_split(const float *x, const uint16_t *g, float eps, in
         case 8192: STG_LAUNCH(rmsnorm_split_rows_kernel<8>, dim3(rows), dim3(256), 0, st, x, g, eps, pair, ld); break;
         default: STG_LAUNCH(rmsnorm_split_kernel, dim3(rows), dim3(256), 0, st, x, g, eps, H, pair, ld);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_split(const float *x, int rows, int n, uint16_t *pair, long ld, hipStream_t st) {
-    if (rows <= 0 || n <= 0) return hipSuccess;
-    if (ld < pair_ld(n)) return hipErrorInvalidValue;
-    if (n % 4 != 0) return hipErrorInvalidValue;
-    STG_LAUNCH(split_kernel, dim3(grid_for((size_t)rows * n / 4)), dim3(256), 0, st, x, rows, n, pair, ld);
     return hipGetLastError();
 }
 

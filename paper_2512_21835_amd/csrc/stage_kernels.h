@@ -126,8 +126,6 @@ size_t gemm_part_floats(int rows, int N, int K, size_t cap64);
 // y = rmsnorm(x) * g as a pair [rows, H] (row stride ld).
 hipError_t launch_rmsnorm_split(const float *x, const uint16_t *g, float eps, int rows, int H, uint16_t *pair,
                                 long ld, hipStream_t st);
-// The pair [rows, n] (row stride ld) of an fp32 matrix [rows, n].
-hipError_t launch_split(const float *x, int rows, int n, uint16_t *pair, long ld, hipStream_t st);
 // silu(gate) * up of gu [rows, 2F] (gate columns first) as a pair [rows, F] (row stride ld).
 hipError_t launch_swiglu_split(const float *gu, int F, int rows, uint16_t *pair, long ld, hipStream_t st);
 
@@ -151,7 +149,7 @@ struct AttnArgs {
     const float *q;      // [rows, Hq d] rotated
     float *out;          // [rows, Hq d]
     // when set, the output goes here instead of `out`, as the hi/lo pair the O projection GEMM reads
-    // ([rows, out_pair_ld], pair_at layout); not for the prefill with an fp32 cache
+    // ([rows, out_pair_ld], pair_at layout)
     uint16_t *out_pair;
     long out_pair_ld;
     float *part_o;       // [rows, Hq, max_splits, d] unnormalised partial outputs
