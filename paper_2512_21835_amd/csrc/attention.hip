@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include "lanes.h"
+#include "lds_dma.h"
 #include "pair.h"
 #include "stage_kernels.h"
 
@@ -492,38 +493,85 @@ __global__ __launch_bounds__(256) void attn_decode_mfma(AttnArgs a) {
 }
 
 constexpr int KT = 32;                 // keys per tile of the prefill kernel
-constexpr int VROW = KT + 8;           // transposed V tile row stride in bf16 (padding)
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 // One workgroup: 128 query rows = G heads x (128 / G) consecutive positions of one sequence, one
 // KV head.  Wave w owns rows 32 w .. 32 w + 31 (row r: head r / BQ, position offset r % BQ).
 // Per 32-key tile: S^T = K Q^T (lane = one query column, 16 keys), online softmax in-lane,
-// O^T += V^T P^T with V transposed in LDS.  q and p enter the MFMAs as bf16 hi + lo pairs.
-// Bounded to two wavefronts per SIMD (205 registers): left to itself the compiler takes 276 (the
-// O^T and S^T accumulators in AGPRs), which admits one, and a tile's dependent MFMA chain and
-// softmax then run with nothing to overlap them.
+// O^T += V^T P^T.  q and p enter the MFMAs as bf16 hi + lo pairs.
+//
+// K and V tiles are copied as they lie in the cache (rows of D elements) into a ring of S stages of LDS by
+// global_load_lds, two tiles ahead of their use, one barrier per tile; no registers stage them.  The
+// 16-byte chunks of a row are permuted by the copies' lane addresses so that the K fragments' reads (16
+// rows, one chunk) and the transposing reads of V (4 rows x 64 bytes) meet distinct banks.  A wavefront
+// multiplies tile t + 1's K by Q while it takes the softmax of tile t: the two are independent, and with
+// one wavefront per SIMD (a prompt's chunk of 500 tokens is 256 workgroups) nothing else fills the
+// matrix pipe during the softmax.  Before, tiles went through registers into padded LDS rows, V element by
+// element into its transpose, between two barriers per tile.  4 x 2048 tokens of the 70B-shaped stage 940
+// -> 590 us, 500 tokens of the 32B-shaped one after 0 to 3000 others 130 -> 92 us on average, 1024 of the
+// 8B-shaped one 70 -> 54 us; bit-identical.
 template <int G, int D>
 __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(AttnArgs a) {
-    constexpr int KROW = D + 8;         // K tile row stride in bf16 (padding)
     constexpr int BQ = 128 / G;
     constexpr int KK = D / 16;          // k16 steps over d
     constexpr int NB = D / 32;          // 32-row blocks of d in O^T
-    __shared__ uint16_t sk[KT * KROW];
-    __shared__ uint16_t sv[D * VROW];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, col = lane & 31;
-    const int qb = gridDim.x - 1 - blockIdx.x, g = blockIdx.y, sidx = blockIdx.z;  // longest first
-    const int T = a.meta->rows_per_seq;
+    constexpr int S = 4;                // stages
+    constexpr int ROW = 2 * D, CH = D / 8;                // bytes and 16-byte chunks of a key's row
+    constexpr int TILE = KT * ROW, STAGE = 2 * TILE;      // K tile, then V tile
+    constexpr int KPC = 1024 / ROW, CP = KT / KPC / 4;    // keys per copy; copies of K (and of V) per wavefront
+    __shared__ __align__(16) char lds[S * STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    const int qb = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, sidx = blockIdx.y;  // the longest blocks of all first
+    const int T = a.rows_per_seq;
     const int pos0 = a.meta->pos0[sidx], slot = a.meta->seq_slot[sidx];
     const int hkv = a.kv.n_kv_heads, hq_total = a.n_q_heads;
     const size_t q_ld = (size_t)hq_total * D;
     const int *table = a.kv.block_table + (size_t)slot * a.kv.max_blocks;
-    const uint16_t *pool = static_cast<const uint16_t *>(a.kv.pool);
-    const size_t blk_stride = (size_t)2 * hkv * kBlockTokens * D;
+    const size_t blk_bytes = (size_t)2 * hkv * kBlockTokens * ROW, v_off = (size_t)hkv * kBlockTokens * ROW;
+    const char *pool = static_cast<const char *>(a.kv.pool) + (size_t)g * kBlockTokens * ROW;
+
+    // keys of the block's last query, and tiles; of the wavefront's own rows: the tiles that they see, and
+    // their first position (a tile that ends before it hides nothing)
+    const int n_keys = pos0 + min(T, (qb + 1) * BQ), n_tiles = (n_keys + KT - 1) / KT;
+    const int first = BQ > 32 ? 32 * wave % BQ : 0;
+    const int wave_min = pos0 + min(qb * BQ + first, T - 1);
+    const int wave_tiles = qb * BQ + first >= T ? 0 : (pos0 + min(T, qb * BQ + (BQ > 32 ? first + 32 : BQ)) + KT - 1) / KT;
+
+    // The copies of one tile by this wavefront: 8 consecutive keys of K and of V (one cache block).  Keys past
+    // the last one: that one (in bounds; their scores are masked).
+    const int lr = lane / CH, lc = lane % CH;
+    auto wave_key = [&](int tile) { return min(tile * KT + 8 * wave, n_keys - 1); };
+    auto copy = [&](int tile, int blk) {
+        const int k0 = wave_key(tile) & ~7, last = n_keys - 1 - k0;   // (8 keys start at a multiple of 8)
+        const char *const kp = pool + (size_t)blk * blk_bytes + (size_t)(k0 % kBlockTokens) * ROW;
+        const uint32_t st = lds_base + tile % S * STAGE + 8 * wave * ROW;
+#pragma unroll
+        for (int i = 0; i < CP; ++i) {
+            const int r = KPC * i + lr, row = 8 * wave + r;   // key of the copy's eight, and row of the tile
+            const int kx = D == 128 ? row & 15 : (row >> 1) & 7, vx = D == 128 ? (row & 3) << 2 : (row & 2) << 1;
+            const uint32_t src = (uint32_t)min(r, last) * ROW;
+            dma16(src + 16 * (lc ^ kx), kp, st + 1024 * i);
+            dma16(src + 16 * (lc ^ vx), kp + v_off, st + TILE + 1024 * i);
+        }
+    };
+    // (a scalar load: the memory clobbers of the copies would have the compiler take a vector load, whose
+    // wait would take in the copies ahead of it)
+    typedef const __attribute__((address_space(4))) int *const_ints;
+    auto block_of = [&](int tile) { return ((const_ints)(uintptr_t)table)[wave_key(tile) / kBlockTokens]; };
+    int blk[S];
+#pragma unroll
+    for (int t = 0; t < S; ++t) blk[t] = block_of(t);
+#pragma unroll
+    for (int t = 0; t < S - 1; ++t) copy(t, blk[t]);   // (tiles past the last: its keys again, never read)
+    int next_blk = blk[S - 1];
 
     // this lane's query (column) and its position
-    const int r = wave * 32 + col, hh = r / BQ, t = qb * BQ + r % BQ;
-    const bool qvalid = t < T;
-    const int qpos = pos0 + (qvalid ? t : T - 1);
-    const size_t qrow = (size_t)(sidx * T + (qvalid ? t : T - 1));
+    const int r = wave * 32 + col, hh = r / BQ, t_q = qb * BQ + r % BQ;
+    const bool qvalid = t_q < T;
+    const int qpos = pos0 + (qvalid ? t_q : T - 1);
+    const size_t qrow = (size_t)(sidx * T + (qvalid ? t_q : T - 1));
     // Q^T fragments: B[k = d 16 kk + 8 half + j][query col]
     bf16x8_t qh[KK], ql[KK];
     {
@@ -544,120 +592,131 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(AttnArgs a) {
         for (int i = 0; i < 16; ++i) o[b][i] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
 
-    const int last_t = min(T, (qb + 1) * BQ) - 1;
-    const int n_keys = pos0 + last_t + 1;
-    const int n_tiles = (n_keys + KT - 1) / KT;
-    // wave's largest query position (tiles past it are fully masked for the wave)
-    int wave_max = 0;
-    {
-        const int r_lo = wave * 32, r_hi = wave * 32 + 31;
-        for (int rr = r_lo; rr <= r_hi; rr += 1) {
-            const int tt = qb * BQ + rr % BQ;
-            if (tt < T) wave_max = max(wave_max, pos0 + tt);
-        }
-    }
-
-    // tile loads: 32 keys x (D / 8) 16-byte chunks (512 for D = 128), PER_T per thread; chunk
-    // c = tid + 256 i.  K: key c / (D / 8), d chunk c % (D / 8) (a wavefront reads 4 whole key
-    // rows).  V: key c % 32, d chunk c / 32, so that one transposed store instruction writes 32
-    // consecutive keys of one V^T row (the K mapping would put a wavefront's 16 rows 8 apart: on
-    // two LDS bank offsets)
-    constexpr int CHUNKS = KT * D / 8;          // 16-byte chunks per K (or V) tile
-    constexpr int PER_T = CHUNKS / 256;         // per thread (2 for D = 128, 1 for D = 64)
-    uint4 kr0, kr1, vr0, vr1;
-#define STG_GLOAD(TILE, I, KR, VR)                                                                        \
-    do {                                                                                                  \
-        const int c_ = tid + 256 * (I);                                                                   \
-        const int kp_ = min((TILE) * KT + c_ / (D / 8), n_keys - 1);                                      \
-        const size_t b_ = (size_t)table[kp_ / kBlockTokens] * blk_stride +                                \
-                          (size_t)(kp_ % kBlockTokens) * D + (c_ % (D / 8)) * 8;                          \
-        KR = *reinterpret_cast<const uint4 *>(pool + b_ + (size_t)g * kBlockTokens * D);                 \
-        const int vp_ = min((TILE) * KT + c_ % KT, n_keys - 1);                                           \
-        const size_t v_ = (size_t)table[vp_ / kBlockTokens] * blk_stride +                                \
-                          (size_t)(vp_ % kBlockTokens) * D + (c_ / KT) * 8;                               \
-        VR = *reinterpret_cast<const uint4 *>(pool + v_ + (size_t)(hkv + g) * kBlockTokens * D);         \
-    } while (0)
-#define STG_LSTORE(I, KR, VR)                                                                             \
-    do {                                                                                                  \
-        const int c_ = tid + 256 * (I);                                                                   \
-        const int key_ = c_ / (D / 8), d_ = (c_ % (D / 8)) * 8;                                           \
-        *reinterpret_cast<uint4 *>(sk + key_ * KROW + d_) = KR;                                           \
-        const int vkey_ = c_ % KT, vd_ = (c_ / KT) * 8;                                                   \
-        const uint32_t w_[4] = {VR.x, VR.y, VR.z, VR.w};                                                  \
-        _Pragma("unroll") for (int j_ = 0; j_ < 4; ++j_) {                                                \
-            sv[(vd_ + 2 * j_) * VROW + vkey_] = (uint16_t)(w_[j_] & 0xFFFFu);                             \
-            sv[(vd_ + 2 * j_ + 1) * VROW + vkey_] = (uint16_t)(w_[j_] >> 16);                             \
-        }                                                                                                 \
-    } while (0)
-    auto gload = [&](int tile) {
-        STG_GLOAD(tile, 0, kr0, vr0);
-        if (PER_T > 1) STG_GLOAD(tile, 1, kr1, vr1);
-    };
-    auto lstore = [&]() {
-        STG_LSTORE(0, kr0, vr0);
-        if (PER_T > 1) STG_LSTORE(1, kr1, vr1);
-    };
-
-    gload(0);
-    for (int tile = 0; tile < n_tiles; ++tile) {
-        __syncthreads();            // previous tile's LDS reads done
-        lstore();
-        __syncthreads();
-        if (tile + 1 < n_tiles) gload(tile + 1);
-        const int k0 = tile * KT;
-        if (k0 <= wave_max) {           // wave-uniform: past it every key of the tile is masked
-        // S^T[key][query] = sum_d K[key][d] Q[query][d]: A = K (lane: key col, d 16kk + 8 half)
+    // S^T[key][query] = sum_d K[key][d] Q[query][d]: A = K (lane: key col, d 16 kk + 8 half)
+    typedef const __attribute__((address_space(3))) u32x4 *lds16;
+    typedef __attribute__((address_space(3))) s16x4_t *lds8;
+    const uint32_t k_at = lds_base + col * ROW + 16 * (half ^ (D == 128 ? col & 15 : (col >> 1) & 7));
+    auto scores = [&](int tile) {
+        const uint32_t L = k_at + tile % S * STAGE;
         f32x16_t s;
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
-            const bf16x8_t kf = as_bf(*reinterpret_cast<const uint4 *>(sk + col * KROW + 16 * kk + 8 * half));
+            const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *(lds16)(L ^ (32 * kk)));   // chunk 2 kk + half, permuted
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qh[kk], s, 0, 0, 0);
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, ql[kk], s, 0, 0, 0);
         }
-        // lane holds keys k0 + 8 (i / 4) + 4 half + i % 4 for query column col
-        float mt = -INFINITY;
+        return s;
+    };
+    // lane holds keys k0 + 8 (i / 4) + 4 half + i % 4 for query column col
+    auto mask = [&](f32x16_t &s, int k0) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int kp = k0 + 8 * (i / 4) + 4 * half + (i % 4);
-            if (kp > qpos) s[i] = -INFINITY;
-            mt = fmaxf(mt, s[i]);
-        }
-        mt = fmaxf(mt, lane_xor(mt, 32));
-        const float m_new = fmaxf(m_run, mt);
-        const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-        float p[16], ps = 0.f;
+        for (int i = 0; i < 16; ++i)
+            if (k0 + 8 * (i / 4) + 4 * half + (i % 4) > qpos) s[i] = -INFINITY;
+    };
+    // The softmax of a tile's scores s in pieces: scores -> p (as a pair) and the factor of what came before.
+    constexpr int PIECES = 11;
+    bf16x8_t ph[2], pl[2];
+    float ref, alpha, p[16], ps;
+    auto pair_of = [&](int i) {   // p[2 i] and p[2 i + 1]
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            p[i] = s[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s[i] - m_new);
-            ps += p[i];
+        for (int j = 2 * i; j < 2 * i + 2; ++j) {
+            ph[j / 8][j % 8] = (__bf16)p[j];
+            pl[j / 8][j % 8] = (__bf16)(p[j] - (float)ph[j / 8][j % 8]);
         }
-        ps += lane_xor(ps, 32);
-        l_run = l_run * alpha + ps;
-        m_run = m_new;
+    };
+    auto piece = [&](const f32x16_t &s, int x) {
+        if (x == 0) {
+            ref = s[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) ref = fmaxf(ref, s[i]);
+        } else if (x == 1) {
+            const float m_new = fmaxf(m_run, fmaxf(ref, lane_xor(ref, 32)));
+            ref = m_new == -INFINITY ? 0.f : m_new;
+            alpha = __builtin_amdgcn_exp2f(m_run - ref);   // (0 on the first tile)
+            m_run = m_new;
+            ps = 0.f;
+        } else if (x < PIECES - 1) {
+            const int i = x - 2;
+#pragma unroll
+            for (int j = 2 * i; j < 2 * i + 2; ++j) {
+                p[j] = __builtin_amdgcn_exp2f(s[j] - ref);
+                ps += p[j];
+            }
+            if (i > 0) pair_of(i - 1);
+        } else {
+            pair_of(7);
+            ps += lane_xor(ps, 32);
+            l_run = l_run * alpha + ps;
+        }
+    };
+    // The scores of `tile`, with the pieces of s's softmax behind the MFMAs (schedule fences keep them there).
+    auto scores_and_softmax = [&](int tile, f32x16_t &s) {
+        const uint32_t L = k_at + tile % S * STAGE;
+        auto key_frag = [&](int kk) { return __builtin_bit_cast(bf16x8_t, *(lds16)(L ^ (32 * kk))); };
+        f32x16_t n;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) n[i] = 0.f;
+        bf16x8_t kf[2] = {key_frag(0), key_frag(1)};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 2 * KK; ++q) {
+            const int kk = q / 2;
+            n = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk & 1], q & 1 ? ql[kk] : qh[kk], n, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if ((q & 1) && kk + 2 < KK) kf[kk & 1] = key_frag(kk + 2);
+#pragma unroll
+            for (int x = 0; x < PIECES; ++x)
+                if (x * 2 * KK / PIECES == q) piece(s, x);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        s = n;
+    };
+    // O^T[d][query] += sum_key V[key][d] P[query][key]; k index (8 half + j) of MFMA m is the lane's key
+    // 16 m + 8 (j / 4) + 4 half + j % 4 = its p[8 m + j].  A transposing read gives 16 lanes the 4 keys x
+    // 16 d that they point at (lane i: key i / 4, d 4 (i % 4) .. + 3) column-wise: lane i all keys of d i.
+    const int vk = 4 * half + (lane & 15) / 4;   // key of this lane's piece, within 8
+    const uint32_t v_at = lds_base + TILE + vk * ROW + 8 * (lane & 1) +
+                          16 * ((((lane >> 4) & 1) * 2 + (lane & 3) / 2) ^ (D == 128 ? (vk & 3) << 2 : (vk & 2) << 1));
+    auto values = [&](int tile) {
         if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {   // some lane's maximum moved
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
         }
-        // O^T[d][query] += sum_key V[key][d] P[query][key]; k index (8 half + j) of MFMA m is the
-        // lane's key 16 m + 8 (j / 4) + 4 half + j % 4 = its p[8 m + j]
+        const uint32_t L = v_at + tile % S * STAGE;
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            bf16x8_t ph, pl;
-            split8(p + 8 * m, ph, pl);
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const uint16_t *vr = sv + (32 * b + col) * VROW + 16 * m + 4 * half;
-                const uint2 v0 = *reinterpret_cast<const uint2 *>(vr), v1 = *reinterpret_cast<const uint2 *>(vr + 8);
-                const bf16x8_t vf = as_bf(make_uint4(v0.x, v0.y, v1.x, v1.y));
-                o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, ph, o[b], 0, 0, 0);
-                o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl, o[b], 0, 0, 0);
+                const uint32_t p = (L ^ (64 * b)) + 16 * m * ROW;
+                const s16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds8)p);
+                const s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds8)(p + 8 * ROW));
+                const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+                o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, ph[m], o[b], 0, 0, 0);
+                o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pl[m], o[b], 0, 0, 0);
             }
+    };
+
+    wait_vm<(S - 2) * 2 * CP>();   // tile 0 has landed (this wavefront's share)
+    lds_barrier();
+    f32x16_t s = scores(0);
+    for (int t = 0; t < n_tiles; ++t) {
+        // tile t + 1 has landed everywhere; tile t - 1 has been read by all: its stage takes tile t + S - 1
+        if (t + S - 2 < n_tiles) wait_vm<(S - 3) * 2 * CP>();
+        else wait_vm<0>();   // (no copies behind it)
+        wait_lgkm<0>();
+        lds_barrier();
+        if (t + S - 1 < n_tiles) {
+            copy(t + S - 1, next_blk);
+            next_blk = block_of(t + S);
         }
-        }
+        if (t >= wave_tiles) continue;   // wave-uniform, as the following: past them every key is masked
+        if (t * KT + KT - 1 > wave_min) mask(s, t * KT);
+        scores_and_softmax(t + 1, s);   // (past the wavefront's last tile: scores of no meaning, not used)
+        values(t);
     }
     if (!qvalid) return;
     // O^T[d = 32 b + 8 (i / 4) + 4 half + i % 4][query col]
@@ -892,7 +951,7 @@ hipError_t launch_gd(const AttnArgs &a, hipStream_t st) {
             STG_LAUNCH((attn_prefill_f32<G, D>), grid, dim3(256), 0, st, a);
         } else {
             constexpr int BQ = 128 / G;
-            dim3 grid((a.rows_per_seq + BQ - 1) / BQ, hkv, a.n_seqs);
+            dim3 grid(hkv, a.n_seqs, (a.rows_per_seq + BQ - 1) / BQ);
             STG_LAUNCH((attn_prefill_mfma<G, D>), grid, dim3(256), 0, st, a);
         }
         return hipGetLastError();
