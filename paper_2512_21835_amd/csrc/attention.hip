@@ -10,6 +10,8 @@
 // cached element and is bound by them); otherwise attn_decode_kernel.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "lanes.h"
 #include "lds_dma.h"
 #include "pair.h"
@@ -204,19 +206,45 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(AttnArgs a) {
     attn_decode_task<G, D, F32KV, FINAL>(a, blockIdx.y, blockIdx.x, blockIdx.z, sm);
 }
 
+// The split states (maximum m, sum l and unnormalised output o of each 64-key split) are merged in a
+// fixed order: groups of kMergeGroup consecutive splits first, then the groups of a lane, then the lanes
+// (attn_merge).  Where a call has splits enough to fill the GPU with a workgroup per group, the splits'
+// kernel writes the groups' states instead of the splits': a quarter of the partial outputs.
+constexpr int kMergeGroup = 4;
+// A group's maximum and its splits' weights exp(m - maximum) (0 for a split without a score above
+// -inf; n splits).
+__device__ __forceinline__ float group_weights(const float m[kMergeGroup], int n, float w[kMergeGroup]) {
+    float mg = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kMergeGroup; ++u)
+        if (u < n) mg = fmaxf(mg, m[u]);
+    const float ref = mg == -INFINITY ? 0.f : mg;
+#pragma unroll
+    for (int u = 0; u < kMergeGroup; ++u) w[u] = expf(m[u] - ref);
+    return mg;
+}
+__device__ __forceinline__ float group_sum(const float v[kMergeGroup], const float w[kMergeGroup], int n) {
+    float s = w[0] * v[0];
+#pragma unroll
+    for (int u = 1; u < kMergeGroup; ++u)
+        if (u < n) s = fmaf(w[u], v[u], s);
+    return s;
+}
+
 // Merge of the decode splits: one workgroup per (row, query head).  Thread t owns the 4 output
-// columns 4 (t % (D/4)) .. + 3 and the splits s with s % SL == t / (D/4) (SL = 1024 / D split
-// lanes: 8 for 128-wide heads, 16 for 64-wide).  Per round of kMergePer splits per lane it issues
-// the loads of all of them at once (addresses clamped to the call's longest row, a.grid_splits),
-// before the row's own split count arrives from the metadata: one round trip for contexts up to
-// kMergePer * SL splits.  A lane merges its splits in ascending order (online: rescaled to the
-// running maximum; weight exp(m_s - max)); the SL lane states then meet in LDS and are added in
-// lane order.  The order depends on the row's split count only, never on the other rows of the
-// call; for a single split the result is exactly o / l (weights exp(0) = 1, empty lanes add 0).
+// columns 4 (t % (D/4)) .. + 3 and the groups with index % SL == t / (D/4) (SL = 1024 / D split
+// lanes: 8 for 128-wide heads, 16 for 64-wide).  Per round it issues the loads of kMergePer states per
+// lane (splits, or with GROUPED whole groups) at once, addresses clamped to the call's longest row
+// (a.grid_splits), before the row's own split count arrives from the metadata: one round trip for
+// contexts up to kMergePer * SL states.  A lane merges its groups in ascending order (online: rescaled
+// to the running maximum); the SL lane states then meet in LDS and are added in lane order.  The order
+// depends on the row's split count only, never on the other rows of the call nor on who combined the
+// groups; for a single split the result is exactly o / l (weights exp(0) = 1, empty lanes add 0).
 constexpr int kMergePer = 8;
-template <int D>
+template <int D, bool GROUPED>
 __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
     constexpr int CG = D / 4, SL = 256 / CG;
+    constexpr int GS = GROUPED ? 1 : kMergeGroup, GPL = kMergePer / GS;   // states per group, groups per lane and round
     __shared__ float s_m[SL][CG], s_l[SL][CG];
     __shared__ float4 s_o[SL][CG];
     const int cg = threadIdx.x % CG, sl = threadIdx.x / CG;
@@ -224,48 +252,59 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
     const size_t pi0 = ((size_t)row * hq_total + hq) * a.max_splits;
     const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml) + pi0;
     const float4 *po = reinterpret_cast<const float4 *>(a.part_o + pi0 * D) + cg;
-    const int lim = a.grid_splits;
+    const int per = GROUPED ? kMergeGroup * a.split_keys : a.split_keys;   // keys per state
+    const int lim = GROUPED ? (a.grid_splits + kMergeGroup - 1) / kMergeGroup : a.grid_splits;
     float mx = -INFINITY, den = 0.f;
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    int nsp = -1;
+    int nst = -1;   // the row's states
     for (int s0 = 0; s0 < lim; s0 += kMergePer * SL) {
-        const int nper = min(kMergePer, (lim - s0 + SL - 1) / SL);  // same for every thread
+        const int ngr = min(GPL, ((lim - s0 + GS - 1) / GS + SL - 1) / SL);  // same for every thread
         float2 v[kMergePer];
         float4 o[kMergePer];
 #pragma unroll
         for (int j = 0; j < kMergePer; ++j)
-            if (j < nper) {
-                const int s = min(s0 + j * SL + sl, lim - 1);
+            if (j / GS < ngr) {
+                const int s = min(s0 + (j / GS * SL + sl) * GS + j % GS, lim - 1);
                 v[j] = ml[s];
                 o[j] = po[(size_t)s * (D / 4)];
             }
-        if (nsp < 0) {
+        if (nst < 0) {
             const int sidx = row / a.rows_per_seq;
             const int ctx = a.meta->pos0[sidx] + row % a.rows_per_seq + 1;
-            nsp = min((ctx + a.split_keys - 1) / a.split_keys, lim);
+            nst = min((ctx + per - 1) / per, lim);
         }
-        if (s0 >= nsp) break;
-        float m = mx;
+        if (s0 >= nst) break;
 #pragma unroll
-        for (int j = 0; j < kMergePer; ++j)
-            if (j < nper && s0 + j * SL + sl < nsp) m = fmaxf(m, v[j].x);
-        if (m > -INFINITY) {  // this lane holds a split of the row
-            const float r = expf(mx - m);  // 0 on the lane's first split (mx = -inf)
-            den *= r;
-            num.x *= r;
-            num.y *= r;
-            num.z *= r;
-            num.w *= r;
+        for (int gi = 0; gi < GPL; ++gi) {
+            const int first = s0 + (gi * SL + sl) * GS, n = min(GS, nst - first);
+            if (gi >= ngr || n <= 0) continue;
+            float mg, lg;
+            float4 og;
+            if constexpr (GROUPED) {
+                mg = v[gi].x;
+                lg = v[gi].y;
+                og = o[gi];
+            } else {
+                float m[GS], w[GS], t[GS];
+                auto sum = [&](auto get) {
 #pragma unroll
-            for (int j = 0; j < kMergePer; ++j)
-                if (j < nper && s0 + j * SL + sl < nsp) {
-                    const float w = expf(v[j].x - m);
-                    den = fmaf(w, v[j].y, den);
-                    num.x = fmaf(w, o[j].x, num.x);
-                    num.y = fmaf(w, o[j].y, num.y);
-                    num.z = fmaf(w, o[j].z, num.z);
-                    num.w = fmaf(w, o[j].w, num.w);
-                }
+                    for (int u = 0; u < GS; ++u) t[u] = get(GS * gi + u);
+                    return group_sum(t, w, n);
+                };
+#pragma unroll
+                for (int u = 0; u < GS; ++u) m[u] = v[GS * gi + u].x;
+                mg = group_weights(m, n, w);
+                lg = sum([&](int j) { return v[j].y; });
+                og = make_float4(sum([&](int j) { return o[j].x; }), sum([&](int j) { return o[j].y; }),
+                                 sum([&](int j) { return o[j].z; }), sum([&](int j) { return o[j].w; }));
+            }
+            const float m = fmaxf(mx, mg), ref = m == -INFINITY ? 0.f : m;
+            const float r = expf(mx - ref), w = expf(mg - ref);  // r = 0 on the lane's first group (mx = -inf)
+            den = fmaf(w, lg, den * r);
+            num.x = fmaf(w, og.x, num.x * r);
+            num.y = fmaf(w, og.y, num.y * r);
+            num.z = fmaf(w, og.z, num.z * r);
+            num.w = fmaf(w, og.w, num.w * r);
             mx = m;
         }
     }
@@ -277,20 +316,18 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
     float M = -INFINITY;
 #pragma unroll
     for (int i = 0; i < SL; ++i) M = fmaxf(M, s_m[i][cg]);
+    const float ref = M == -INFINITY ? 0.f : M;
     float L = 0.f;
     float4 O = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int i = 0; i < SL; ++i) {
-        const float mi = s_m[i][cg];
-        if (mi > -INFINITY) {
-            const float w = expf(mi - M);
-            const float4 oi = s_o[i][cg];
-            L = fmaf(w, s_l[i][cg], L);
-            O.x = fmaf(w, oi.x, O.x);
-            O.y = fmaf(w, oi.y, O.y);
-            O.z = fmaf(w, oi.z, O.z);
-            O.w = fmaf(w, oi.w, O.w);
-        }
+        const float w = expf(s_m[i][cg] - ref);   // (a lane without a group: 0, and its sums are 0)
+        const float4 oi = s_o[i][cg];
+        L = fmaf(w, s_l[i][cg], L);
+        O.x = fmaf(w, oi.x, O.x);
+        O.y = fmaf(w, oi.y, O.y);
+        O.z = fmaf(w, oi.z, O.z);
+        O.w = fmaf(w, oi.w, O.w);
     }
     const float4 v = make_float4(O.x / L, O.y / L, O.z / L, O.w / L);
     const int col = hq * D + 4 * cg;
@@ -317,28 +354,31 @@ __device__ __forceinline__ void split8(const float *x, bf16x8_t &hi, bf16x8_t &l
 
 // 16 bytes that one workgroup reads once per call, non-temporal (16 rows at 7900 tokens of the 70B-shaped
 // stage 118.6 -> 116 us, 64 at about 830 of the 8B-shaped one 44.8 -> 42.8).
-__device__ __forceinline__ uint4 load_stream16(const uint16_t *p) {
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
+__device__ __forceinline__ u32x4 load_stream16(const uint16_t *p) {
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
 }
 
-// Decode attention of one (64-key split, KV head g, row) on the matrix cores (bf16 KV, D = 128,
-// G <= 16): S^T = K Q^T with the K rows of the split's cache blocks as the A operand (one 16-key
-// block per wavefront) and Q as a bf16 hi/lo pair; softmax statistics per head from the MFMA
-// layout; O = P V with P (hi/lo) from LDS and V read transposed from an LDS tile.  Partial
-// outputs as attn_decode_task writes them, or with FINAL the output o / l.
-template <int G, int D, bool FINAL>
-__global__ __launch_bounds__(256) void attn_decode_mfma(AttnArgs a) {
+// Decode attention of (up to UNITS consecutive 64-key splits, KV head g, row) on the matrix cores (bf16
+// KV, D = 128, G <= 16): S^T = K Q^T with the K rows of the split's cache blocks as the A operand (one
+// 16-key block per wavefront) and Q as a bf16 hi/lo pair; softmax statistics per head from the MFMA
+// layout; O = P V with P (hi/lo) from LDS and V read transposed from an LDS tile.  UNITS == 1: partial
+// outputs as attn_decode_task writes them, or with FINAL the output o / l.  UNITS == kMergeGroup: the
+// state of the whole group of splits, combined as attn_merge combines the splits' own (the same bits),
+// with the K (V) rows of the next split loaded while this one is multiplied.
+template <int G, int D, bool FINAL, int UNITS>
+__global__ __launch_bounds__(256, UNITS == 1 ? 5 : 4) void attn_decode_mfma(AttnArgs a) {
     static_assert(D == 128 && G <= 16, "one 128-wide head, up to 16 query heads per KV head");
+    static_assert(UNITS == 1 || (UNITS == kMergeGroup && !FINAL), "one split, or a merge group");
     constexpr int VROW = D + 8;                     // V tile row stride in bf16 (272 bytes)
-    // one LDS area for the K tile (until the first barrier: each wavefront reads only its own 16
-    // keys) and then the V tile
-    __shared__ uint4 kv_tile[kChunk * VROW * 2 / 16];
-    uint4 (*const ks)[D / 8] = reinterpret_cast<uint4 (*)[D / 8]>(kv_tile);    // [key][chunk ^ key % 16]
-    uint16_t (*const vs)[VROW] = reinterpret_cast<uint16_t (*)[VROW]>(kv_tile);
+    // UNITS == 1: one LDS area for the K tile (until the first barrier: each wavefront reads only its
+    // own 16 keys) and then the V tile
+    __shared__ uint4 v_tile[kChunk * VROW * 2 / 16];
+    __shared__ uint4 k_tile[UNITS > 1 ? kChunk * D * 2 / 16 : 1];
+    uint4 (*const ks)[D / 8] = reinterpret_cast<uint4 (*)[D / 8]>(UNITS > 1 ? k_tile : v_tile);   // [key][chunk ^ key % 16]
+    uint16_t (*const vs)[VROW] = reinterpret_cast<uint16_t (*)[VROW]>(v_tile);
     __shared__ uint4 pf[2][2][64];                  // P A-fragments [key step][hi, lo][lane]
-    __shared__ float wm[4][16], wl[4][16];
-    const int split = blockIdx.y, g = blockIdx.x, row = blockIdx.z;
+    __shared__ float wm[UNITS][4][16], wl[UNITS][4][16];
+    const int split0 = blockIdx.y * UNITS, g = blockIdx.x, row = blockIdx.z;
     const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int hq_total = a.n_q_heads, hkv = a.kv.n_kv_heads;
@@ -354,30 +394,41 @@ __global__ __launch_bounds__(256) void attn_decode_mfma(AttnArgs a) {
     const int sidx = row / a.rows_per_seq;
     const int pos = a.meta->pos0[sidx] + row % a.rows_per_seq;
     const int slot = a.meta->seq_slot[sidx];
-    const int ctx = pos + 1, kbeg = split * a.split_keys;
-    if (kbeg >= ctx || slot < 0) return;  // (slot tested so that both metadata loads go out together)
-    const int n = min(a.split_keys, ctx - kbeg);
+    const int ctx = pos + 1, kbeg0 = split0 * a.split_keys;
+    if (kbeg0 >= ctx || slot < 0) return;  // (slot tested so that both metadata loads go out together)
+    const int units = UNITS > 1 ? min(UNITS, (ctx - kbeg0 + a.split_keys - 1) / a.split_keys) : 1;
     const size_t blk_stride = (size_t)2 * hkv * kBlockTokens * D;
     const uint16_t *pool = static_cast<const uint16_t *>(a.kv.pool);
-    // every key of wavefront w (16 w .. 16 w + 15 of the split, clamped into it) lies in one cache
-    // block (splits start on a block boundary): one block-table entry per wavefront
-    const int blk = a.kv.block_table[(size_t)slot * a.kv.max_blocks + (kbeg + min(16 * wave, n - 1)) / kBlockTokens];
-    const uint16_t *kb = pool + (size_t)blk * blk_stride + (size_t)g * kBlockTokens * D;
-    const uint16_t *vb = pool + (size_t)blk * blk_stride + (size_t)(hkv + g) * kBlockTokens * D;
+    // every key of wavefront w (16 w .. 16 w + 15 of a split, clamped into it) lies in one cache
+    // block (splits start on a block boundary): one block-table entry per wavefront and split
+    const int *table = a.kv.block_table + (size_t)slot * a.kv.max_blocks;
+    int blk[UNITS];
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u)
+        blk[u] = table[min(kbeg0 + u * a.split_keys + 16 * wave, ctx - 1) / kBlockTokens];
     // K and V rows, 4 keys x 256 contiguous bytes per load instruction (16 keys x 64 bytes, the
     // MFMA fragment layout read straight from memory, streams poorly): instruction i, lane l: key
     // 16 wave + 4 i + lq of the split (clamped into it); K: 16-byte d chunk l16 ^ (4 i + lq),
     // stored in the K tile at [key][l16]; V: chunk l16
-    auto krow = [&](int i) {
-        const int key = kbeg + min(16 * wave + 4 * i + lq, n - 1);
-        return load_stream16(kb + (size_t)(key % kBlockTokens) * D + 8 * (l16 ^ (4 * i + lq)));
+    u32x4 kr[4], vr[4];
+    auto load_k = [&](int u) {
+        const uint16_t *kb = pool + (size_t)blk[u] * blk_stride + (size_t)g * kBlockTokens * D;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int key = min(kbeg0 + u * a.split_keys + 16 * wave + 4 * i + lq, ctx - 1);
+            kr[i] = load_stream16(kb + (size_t)(key % kBlockTokens) * D + 8 * (l16 ^ (4 * i + lq)));
+        }
     };
-    auto vrow = [&](int i) {
-        const int key = kbeg + min(16 * wave + 4 * i + lq, n - 1);
-        return load_stream16(vb + (size_t)(key % kBlockTokens) * D + 8 * l16);
+    auto load_v = [&](int u) {
+        const uint16_t *vb = pool + (size_t)blk[u] * blk_stride + (size_t)(hkv + g) * kBlockTokens * D;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int key = min(kbeg0 + u * a.split_keys + 16 * wave + 4 * i + lq, ctx - 1);
+            vr[i] = load_stream16(vb + (size_t)(key % kBlockTokens) * D + 8 * l16);
+        }
     };
-    const uint4 kr0 = krow(0), kr1 = krow(1), kr2 = krow(2), kr3 = krow(3);
-    const uint4 vr0 = vrow(0), vr1 = vrow(1), vr2 = vrow(2), vr3 = vrow(3);
+    load_k(0);
+    load_v(0);
     // every K and V load in flight before any is used (left alone, the scheduler issues half of
     // them after the first products, a second round trip to memory)
     __builtin_amdgcn_sched_barrier(0);
@@ -393,92 +444,104 @@ __global__ __launch_bounds__(256) void attn_decode_mfma(AttnArgs a) {
         for (int j = 0; j < 8; ++j) x[j] = l16 < G ? q8[j] * scale : 0.f;
         split8(x, qh[s], ql[s]);
     }
-    ks[16 * wave + lq][l16] = kr0;
-    ks[16 * wave + 4 + lq][l16] = kr1;
-    ks[16 * wave + 8 + lq][l16] = kr2;
-    ks[16 * wave + 12 + lq][l16] = kr3;
-    // K fragments: key 16 wave + l16, d 32 s + 8 lq, i.e. chunk 4 s + lq (the tile holds chunk c of
-    // key k at c ^ k % 16: every 16 lanes of a read meet distinct banks)
-    f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
+    // o[u][nb][i]: split u, head 4 lq + i, d 32 wave + 16 nb + l16
+    f32x4_t o[UNITS][2];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const bf16x8_t kf = as_bf(ks[16 * wave + l16][(4 * s + lq) ^ l16]);
-        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qh[s], sc, 0, 0, 0);
-        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, ql[s], sc, 0, 0, 0);
-    }
-    // sc[i]: score of key 16 wave + 4 lq + i for head l16
-    float mx = -INFINITY;
+    for (int u = 0; u < UNITS; ++u) {
+        if (u > 0 && u >= units) break;
+        const int n = min(a.split_keys, ctx - kbeg0 - u * a.split_keys);
+        const bool more = u + 1 < UNITS && u + 1 < units;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (16 * wave + 4 * lq + i >= n) sc[i] = -INFINITY;
-        mx = fmaxf(mx, sc[i]);
-    }
-    mx = fmaxf(mx, lane_xor(mx, 16));
-    mx = fmaxf(mx, lane_xor(mx, 32));
-    if (lane < 16) wm[wave][lane] = mx;
-    __syncthreads();   // every wavefront's K reads done: the tile takes V
-    *reinterpret_cast<uint4 *>(&vs[16 * wave + lq][8 * l16]) = vr0;
-    *reinterpret_cast<uint4 *>(&vs[16 * wave + 4 + lq][8 * l16]) = vr1;
-    *reinterpret_cast<uint4 *>(&vs[16 * wave + 8 + lq][8 * l16]) = vr2;
-    *reinterpret_cast<uint4 *>(&vs[16 * wave + 12 + lq][8 * l16]) = vr3;
-    const float mh = fmaxf(fmaxf(wm[0][l16], wm[1][l16]), fmaxf(wm[2][l16], wm[3][l16]));
-    float p[4], ls = 0.f;
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4 *>(&ks[16 * wave + 4 * i + lq][l16]) = kr[i];
+        if (more) load_k(u + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        // K fragments: key 16 wave + l16, d 32 s + 8 lq, i.e. chunk 4 s + lq (the tile holds chunk c of
+        // key k at c ^ k % 16: every 16 lanes of a read meet distinct banks)
+        f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        p[i] = sc[i] == -INFINITY ? 0.f : expf(sc[i] - mh);
-        ls += p[i];
-    }
-    ls += lane_xor(ls, 16);
-    ls += lane_xor(ls, 32);
-    if (lane < 16) wl[wave][lane] = ls;
-    // P fragment slot of key 16 wave + 4 lq + i: key step wave / 2, lane l16 + 16 (2 (wave % 2) + lq / 2),
-    // elements 4 (lq % 2) + i
-    {
-        uint16_t hb[4], lb[4];
+        for (int s = 0; s < 4; ++s) {
+            const bf16x8_t kf = as_bf(ks[16 * wave + l16][(4 * s + lq) ^ l16]);
+            sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qh[s], sc, 0, 0, 0);
+            sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, ql[s], sc, 0, 0, 0);
+        }
+        // sc[i]: score of key 16 wave + 4 lq + i for head l16
+        float mx = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const __bf16 h = (__bf16)p[i];
-            const __bf16 l = (__bf16)(p[i] - (float)h);
-            hb[i] = __builtin_bit_cast(uint16_t, h);
-            lb[i] = __builtin_bit_cast(uint16_t, l);
+            if (16 * wave + 4 * lq + i >= n) sc[i] = -INFINITY;
+            mx = fmaxf(mx, sc[i]);
         }
-        const int L = l16 + 16 * (2 * (wave & 1) + (lq >> 1));
-        uint2 h2 = make_uint2(hb[0] | ((uint32_t)hb[1] << 16), hb[2] | ((uint32_t)hb[3] << 16));
-        uint2 l2 = make_uint2(lb[0] | ((uint32_t)lb[1] << 16), lb[2] | ((uint32_t)lb[3] << 16));
-        reinterpret_cast<uint2 *>(&pf[wave >> 1][0][L])[lq & 1] = h2;
-        reinterpret_cast<uint2 *>(&pf[wave >> 1][1][L])[lq & 1] = l2;
-    }
-    __syncthreads();
-    // O block (heads 0..15) x (d 32 wave + 16 nb .. + 15), K = the split's 64 keys in two steps
-    f32x4_t o[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        mx = fmaxf(mx, lane_xor(mx, 16));
+        mx = fmaxf(mx, lane_xor(mx, 32));
+        if (lane < 16) wm[u][wave][lane] = mx;
+        // every wavefront's K reads (UNITS == 1) and its reads of the last split's V and P are done
+        __syncthreads();
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-        const bf16x8_t ph = as_bf(pf[ks][0][lane]), pl = as_bf(pf[ks][1][lane]);
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4 *>(&vs[16 * wave + 4 * i + lq][8 * l16]) = vr[i];
+        if (more) load_v(u + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const float mh = fmaxf(fmaxf(wm[u][0][l16], wm[u][1][l16]), fmaxf(wm[u][2][l16], wm[u][3][l16]));
+        float p[4], ls = 0.f;
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            const int d = 32 * wave + 16 * nb + l16;
-            bf16x8_t vb;
+        for (int i = 0; i < 4; ++i) {
+            p[i] = sc[i] == -INFINITY ? 0.f : expf(sc[i] - mh);
+            ls += p[i];
+        }
+        ls += lane_xor(ls, 16);
+        ls += lane_xor(ls, 32);
+        if (lane < 16) wl[u][wave][lane] = ls;
+        // P fragment slot of key 16 wave + 4 lq + i: key step wave / 2, lane l16 + 16 (2 (wave % 2) + lq / 2),
+        // elements 4 (lq % 2) + i
+        {
+            uint16_t hb[4], lb[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) vb[j] = __builtin_bit_cast(__bf16, vs[32 * ks + 8 * lq + j][d]);
-            o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, vb, o[nb], 0, 0, 0);
-            o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, vb, o[nb], 0, 0, 0);
+            for (int i = 0; i < 4; ++i) {
+                const __bf16 h = (__bf16)p[i];
+                const __bf16 l = (__bf16)(p[i] - (float)h);
+                hb[i] = __builtin_bit_cast(uint16_t, h);
+                lb[i] = __builtin_bit_cast(uint16_t, l);
+            }
+            const int L = l16 + 16 * (2 * (wave & 1) + (lq >> 1));
+            uint2 h2 = make_uint2(hb[0] | ((uint32_t)hb[1] << 16), hb[2] | ((uint32_t)hb[3] << 16));
+            uint2 l2 = make_uint2(lb[0] | ((uint32_t)lb[1] << 16), lb[2] | ((uint32_t)lb[3] << 16));
+            reinterpret_cast<uint2 *>(&pf[wave >> 1][0][L])[lq & 1] = h2;
+            reinterpret_cast<uint2 *>(&pf[wave >> 1][1][L])[lq & 1] = l2;
+        }
+        __syncthreads();
+        // O block (heads 0..15) x (d 32 wave + 16 nb .. + 15), K = the split's 64 keys in two steps
+        o[u][0] = o[u][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const bf16x8_t ph = as_bf(pf[t][0][lane]), pl = as_bf(pf[t][1][lane]);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                const int d = 32 * wave + 16 * nb + l16;
+                bf16x8_t vb;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) vb[j] = __builtin_bit_cast(__bf16, vs[32 * t + 8 * lq + j][d]);
+                o[u][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, vb, o[u][nb], 0, 0, 0);
+                o[u][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, vb, o[u][nb], 0, 0, 0);
+            }
         }
     }
-    // o[nb][i]: head 4 lq + i, d 32 wave + 16 nb + l16
+    auto unit_max = [&](int u, int h) {
+        return fmaxf(fmaxf(wm[u][0][h], wm[u][1][h]), fmaxf(wm[u][2][h], wm[u][3][h]));
+    };
+    auto unit_sum = [&](int u, int h) { return ((wl[u][0][h] + wl[u][1][h]) + wl[u][2][h]) + wl[u][3][h]; };
     if (FINAL) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int h = 4 * lq + i;
             if (h >= G) continue;
-            const float l_sum = ((wl[0][h] + wl[1][h]) + wl[2][h]) + wl[3][h];
+            const float l_sum = unit_sum(0, h);
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) {
                 const int col = (g * G + h) * D + 32 * wave + 16 * nb + l16;
                 if (a.out_pair) {
                     uint16_t *p = a.out_pair + row * a.out_pair_ld + pair_at(col);
-                    split_pair(o[nb][i] / l_sum, p[0], p[32]);
+                    split_pair(o[0][nb][i] / l_sum, p[0], p[32]);
                 } else {
-                    a.out[(size_t)row * hq_total * D + col] = o[nb][i] / l_sum;
+                    a.out[(size_t)row * hq_total * D + col] = o[0][nb][i] / l_sum;
                 }
             }
         }
@@ -488,14 +551,34 @@ __global__ __launch_bounds__(256) void attn_decode_mfma(AttnArgs a) {
     for (int i = 0; i < 4; ++i) {
         const int h = 4 * lq + i;
         if (h >= G) continue;
-        const size_t pi = ((size_t)row * hq_total + g * G + h) * a.max_splits + split;
+        const size_t pi = ((size_t)row * hq_total + g * G + h) * a.max_splits + blockIdx.y;
+        if constexpr (UNITS == 1) {
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) a.part_o[pi * D + 32 * wave + 16 * nb + l16] = o[nb][i];
-    }
-    if (wave == 0 && lane < G) {
-        const size_t pi = ((size_t)row * hq_total + g * G + lane) * a.max_splits + split;
-        a.part_ml[pi * 2 + 0] = fmaxf(fmaxf(wm[0][lane], wm[1][lane]), fmaxf(wm[2][lane], wm[3][lane]));
-        a.part_ml[pi * 2 + 1] = ((wl[0][lane] + wl[1][lane]) + wl[2][lane]) + wl[3][lane];
+            for (int nb = 0; nb < 2; ++nb) a.part_o[pi * D + 32 * wave + 16 * nb + l16] = o[0][nb][i];
+            if (wave == 0 && l16 == 0) {
+                a.part_ml[pi * 2 + 0] = unit_max(0, h);
+                a.part_ml[pi * 2 + 1] = unit_sum(0, h);
+            }
+        } else {
+            float m[UNITS], l[UNITS], w[UNITS];
+#pragma unroll
+            for (int u = 0; u < UNITS; ++u) m[u] = u < units ? unit_max(u, h) : -INFINITY;
+            const float mg = group_weights(m, units, w);
+#pragma unroll
+            for (int u = 0; u < UNITS; ++u) l[u] = u < units ? unit_sum(u, h) : 0.f;
+            const float lg = group_sum(l, w, units);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                float v[UNITS];
+#pragma unroll
+                for (int u = 0; u < UNITS; ++u) v[u] = u < units ? o[u][nb][i] : 0.f;
+                a.part_o[pi * D + 32 * wave + 16 * nb + l16] = group_sum(v, w, units);
+            }
+            if (wave == 0 && l16 == 0) {
+                a.part_ml[pi * 2 + 0] = mg;
+                a.part_ml[pi * 2 + 1] = lg;
+            }
+        }
     }
 }
 
@@ -963,33 +1046,50 @@ hipError_t launch_gd(const AttnArgs &a, hipStream_t st) {
         }
         return hipGetLastError();
     }
-    if (a.split_keys > kChunk || a.split_keys % kBlockTokens || a.max_splits > kMaxDecodeSplits ||
-        a.rows_per_seq <= 0)
+    if (a.split_keys != kChunk || a.max_splits > kMaxDecodeSplits || a.rows_per_seq <= 0)
         return hipErrorInvalidValue;
     // KV heads fastest: workgroups that start together read the heads of the same cache blocks, which lie
     // side by side (64 KB of a 70B-shaped block, 4 KB per head and workgroup).  With the splits fastest they read the
     // same 4 KB of every 64: 16 rows at 7900 tokens of the 70B-shaped stage 116 -> 99 us, 8 rows at 7000 of
     // the 8B-shaped one 44 -> 40.
     dim3 grid(hkv, a.grid_splits, a.rows);
+    auto merge = [&](auto grouped) {
+        STG_LAUNCH((attn_merge<D, decltype(grouped)::value>), dim3((unsigned)a.n_q_heads, (unsigned)a.rows), dim3(256), 0, st, a);
+        return hipGetLastError();
+    };
     if (a.grid_splits == 1) {   // every row within one split: its output directly, no merge
         if (a.kv_fp32)
             STG_LAUNCH((attn_decode_kernel<G, D, true, true>), grid, dim3(256), 0, st, a);
         else if constexpr (D == 128)
-            STG_LAUNCH((attn_decode_mfma<G, D, true>), grid, dim3(256), 0, st, a);
+            STG_LAUNCH((attn_decode_mfma<G, D, true, 1>), grid, dim3(256), 0, st, a);
         else
             STG_LAUNCH((attn_decode_kernel<G, D, false, true>), grid, dim3(256), 0, st, a);
         return hipGetLastError();
     }
+    if constexpr (D == 128) {
+        // A workgroup per group of splits where there are at least 48 group outputs per compute unit (groups of
+        // the longest row x query heads x rows): the partial outputs, 512 bytes per split and query head written
+        // and read again, then cost more than what the larger workgroups lose (with four wavefronts per SIMD
+        // instead of five, and a coarser last round).  Splits and merge, a workgroup per split -> per group:
+        // 70B-shaped 16 rows at 7900 tokens (31744 outputs) 113 -> 104 us, 32 at 2000 (16384) 61.9 -> 57.5,
+        // 8 at 7900 (15872) 60.2 -> 57.8, 8B-shaped 64 at 2000 (16384) 101 -> 96; below, 64 at 1100 (10240) 59.9
+        // against 61.9, 16 at 4000 (8192) 52.0 against 54.6, 13B-shaped 16 at 2000 (5120) 105.8 against 111.
+        const int groups = (a.grid_splits + kMergeGroup - 1) / kMergeGroup;
+        if (!a.kv_fp32 && (long)groups * a.n_q_heads * a.rows >= 48L * device_compute_units()) {
+            grid.y = groups;
+            STG_LAUNCH((attn_decode_mfma<G, D, false, kMergeGroup>), grid, dim3(256), 0, st, a);
+            const hipError_t e = hipGetLastError();
+            return e != hipSuccess ? e : merge(std::true_type{});
+        }
+    }
     if (a.kv_fp32)
         STG_LAUNCH((attn_decode_kernel<G, D, true, false>), grid, dim3(256), 0, st, a);
     else if constexpr (D == 128)
-        STG_LAUNCH((attn_decode_mfma<G, D, false>), grid, dim3(256), 0, st, a);
+        STG_LAUNCH((attn_decode_mfma<G, D, false, 1>), grid, dim3(256), 0, st, a);
     else
         STG_LAUNCH((attn_decode_kernel<G, D, false, false>), grid, dim3(256), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    STG_LAUNCH((attn_merge<D>), dim3((unsigned)a.n_q_heads, (unsigned)a.rows), dim3(256), 0, st, a);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : merge(std::false_type{});
 }
 
 }  // namespace
