@@ -79,8 +79,8 @@ __device__ __forceinline__ void attn_decode_task(const AttnArgs &a, int split, i
         for (int j = 0; j < 8; ++j) q[h][j] = qp[j] * scale;
     }
     const int sidx = row / a.rows_per_seq;
-    const int pos = a.meta->pos0[sidx] + row % a.rows_per_seq;
-    const int slot = a.meta->seq_slot[sidx];
+    const int pos = a.meta.pos0(sidx) + row % a.rows_per_seq;
+    const int slot = a.meta.seq_slot(sidx);
     const int ctx = pos + 1;
     const int kbeg = split * a.split_keys;
     if (kbeg >= ctx || slot < 0) return;  // (slot tested so that both metadata loads go out together)
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
             }
         if (nst < 0) {
             const int sidx = row / a.rows_per_seq;
-            const int ctx = a.meta->pos0[sidx] + row % a.rows_per_seq + 1;
+            const int ctx = a.meta.pos0(sidx) + row % a.rows_per_seq + 1;
             nst = min((ctx + per - 1) / per, lim);
         }
         if (s0 >= nst) break;
@@ -392,8 +392,8 @@ __global__ __launch_bounds__(256, UNITS == 1 ? 5 : 4) void attn_decode_mfma(Attn
         qv[s][1] = *reinterpret_cast<const float4 *>(qp + 32 * s + 4);
     }
     const int sidx = row / a.rows_per_seq;
-    const int pos = a.meta->pos0[sidx] + row % a.rows_per_seq;
-    const int slot = a.meta->seq_slot[sidx];
+    const int pos = a.meta.pos0(sidx) + row % a.rows_per_seq;
+    const int slot = a.meta.seq_slot(sidx);
     const int ctx = pos + 1, kbeg0 = split0 * a.split_keys;
     if (kbeg0 >= ctx || slot < 0) return;  // (slot tested so that both metadata loads go out together)
     const int units = UNITS > 1 ? min(UNITS, (ctx - kbeg0 + a.split_keys - 1) / a.split_keys) : 1;
@@ -615,7 +615,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(AttnArgs a) {
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const int qb = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, sidx = blockIdx.y;  // the longest blocks of all first
     const int T = a.rows_per_seq;
-    const int pos0 = a.meta->pos0[sidx], slot = a.meta->seq_slot[sidx];
+    const int pos0 = a.meta.pos0(sidx), slot = a.meta.seq_slot(sidx);
     const int hkv = a.kv.n_kv_heads, hq_total = a.n_q_heads;
     const size_t q_ld = (size_t)hq_total * D;
     const int *table = a.kv.block_table + (size_t)slot * a.kv.max_blocks;
@@ -853,7 +853,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wq = wave & 1, kh = wave >> 1;
     const int qb = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, sidx = blockIdx.y;  // the longest blocks of all first
     const int T = a.rows_per_seq;
-    const int pos0 = a.meta->pos0[sidx], slot = a.meta->seq_slot[sidx];
+    const int pos0 = a.meta.pos0(sidx), slot = a.meta.seq_slot(sidx);
     const int hkv = a.kv.n_kv_heads, hq_total = a.n_q_heads;
     const size_t q_ld = (size_t)hq_total * D;
     const int *table = a.kv.block_table + (size_t)slot * a.kv.max_blocks;

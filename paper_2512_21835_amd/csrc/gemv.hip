@@ -135,15 +135,15 @@ __device__ __forceinline__ EpiIn epi_load(const GemvArgs &a, int u, int m) {
         const int d = a.kv.head_dim, half = d / 2;
         const int h = u / half, i = u % half;
         const int row = a.row0 + m;
-        const int sidx = row / a.meta->rows_per_seq;
-        const int pos = a.meta->pos0[sidx] + row % a.meta->rows_per_seq;
+        const int sidx = row / a.meta.rows_per_seq;
+        const int pos = a.meta.pos0(sidx) + row % a.meta.rows_per_seq;
         const int hq = a.n_q_heads, hkv = a.kv.n_kv_heads;
         if (h < hq + hkv) {
             e.c = a.cos_t[(size_t)pos * half + i];
             e.s = a.sin_t[(size_t)pos * half + i];
         }
         if (h >= hq) {
-            const int slot = a.meta->seq_slot[sidx];
+            const int slot = a.meta.seq_slot(sidx);
             const int block = a.kv.block_table[(size_t)slot * a.kv.max_blocks + pos / kBlockTokens];
             const int kv = h < hq + hkv ? 0 : 1;
             const int g = h - hq - kv * hkv;

@@ -39,9 +39,9 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(RopeKvArgs a) {
     if (t >= rot + hkv * 2 * per) return;
     const size_t ld = (size_t)(hq + 2 * hkv) * d, stride = (size_t)a.rows * ld;
     const float *src = a.qkv + row * ld;
-    const int sidx = row / a.meta->rows_per_seq;
-    const int pos = a.meta->pos0[sidx] + row % a.meta->rows_per_seq;
-    const int slot = a.meta->seq_slot[sidx];
+    const int sidx = row / a.meta.rows_per_seq;
+    const int pos = a.meta.pos0(sidx) + row % a.meta.rows_per_seq;
+    const int slot = a.meta.seq_slot(sidx);
     const size_t head_stride = (size_t)kBlockTokens * d;
     auto cache = [&]() {   // the row's position of head 0 of K
         const int block = a.kv.block_table[(size_t)slot * a.kv.max_blocks + pos / kBlockTokens];

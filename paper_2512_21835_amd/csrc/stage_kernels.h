@@ -34,6 +34,17 @@ struct CallMeta {
     int pos0[kMaxSeqs];
 };
 
+// Where a kernel finds a call's rows: in the device copy of its metadata, or, for a call of one sequence,
+// here.  Such a call, the one whose latency counts, then needs no launch that writes the metadata, and its
+// kernels have one dependent load less ahead of the block table's (70B-shaped layer, four calls of one row
+// 1078 -> 1069 us; tiny stage's 16-token prompt and 16 steps 739 -> 711).
+struct RowMap {
+    const CallMeta *seqs;   // null: one sequence
+    int rows_per_seq, slot, first;
+    __device__ __forceinline__ int pos0(int seq) const { return seqs ? seqs->pos0[seq] : first; }
+    __device__ __forceinline__ int seq_slot(int seq) const { return seqs ? seqs->seq_slot[seq] : slot; }
+};
+
 // Paged KV pool of one layer: block b holds K then V, each [n_kv_heads][16][head_dim].
 struct KvView {
     void *pool;              // element type: bf16 bits or fp32 (kv_fp32)
@@ -66,7 +77,7 @@ struct GemvArgs {
     KvView kv;
     int n_q_heads;
     int kv_fp32;
-    const CallMeta *meta;  // device copy of the call's row metadata
+    RowMap meta;
     // Matrix-core launches split K across workgroups when given this workspace (and the layer
     // shape calls for it): [8][2][16][units] partial products, [8][16] partial sums of squares.
     float *split_part;
@@ -138,7 +149,7 @@ struct RopeKvArgs {
     int n_q_heads;
     int kv_fp32;
     int rows;
-    const CallMeta *meta; // device copy of the call's row metadata
+    RowMap meta;
 };
 hipError_t launch_rope_kv_store(const RopeKvArgs &a, hipStream_t st);
 // The QKV projection and what follows it (r.qkv and r.n_part are set here): g.out is where an uncut
@@ -163,13 +174,13 @@ struct AttnArgs {
     int grid_splits;     // splits launched: ceil(longest context in the call / split_keys)
     int n_seqs;          // sequences in the call and rows per sequence: host copies of the row
     int rows_per_seq;    // metadata (the prefill launch grid; the decode kernels' row -> sequence map)
-    const CallMeta *meta; // device copy of the call's row metadata
+    RowMap meta;
 };
 hipError_t launch_attention(const AttnArgs &a, hipStream_t st);
 bool attention_supported(int group, int head_dim);
 
-// Writes the call's row metadata to device memory (one small launch per call; the hot kernels
-// read it from there instead of carrying it in their arguments).
+// Writes the call's row metadata to device memory (one small launch per call of several sequences; the hot
+// kernels read it from there instead of carrying it in their arguments).
 hipError_t launch_meta_write(const CallMeta &m, CallMeta *dst, hipStream_t st);
 
 // Slot tags (stage_config.slot_check): tag = {layer, load}, two ints.  The check compares a tag

@@ -741,13 +741,13 @@ struct LayerWeights {
     long long load = -1;    // its load number (slot tag check)
 };
 
-int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int T, const CallMeta *meta,
+int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int T, const RowMap &meta,
                       int grid_splits, const float *x_src, float *x_dst);
 
 // One layer's kernels.  Under STAGE_TIME_LAYERS the MHA-block kernels and the MLP-block kernels
 // are bracketed by events separately, so that a wait for the MLP block between them is not
 // counted as compute.
-int run_layer(stage *s, int layer, const LayerWeights &w, int rows, int T, const CallMeta *meta,
+int run_layer(stage *s, int layer, const LayerWeights &w, int rows, int T, const RowMap &meta,
               int grid_splits, const float *x_src, float *x_dst) {
     if (!(s->cfg.timing & STAGE_TIME_LAYERS))
         return run_layer_kernels(s, layer, w, rows, T, meta, grid_splits, x_src, x_dst);
@@ -784,7 +784,7 @@ int mlp_boundary(stage *s, int layer, const LayerWeights &w) {
     return STAGE_OK;
 }
 
-RopeKvArgs rope_args(stage *s, int layer, int rows, const CallMeta *meta) {
+RopeKvArgs rope_args(stage *s, int layer, int rows, const RowMap &meta) {
     RopeKvArgs r{};
     r.q_out = s->ws_q;
     r.cos_t = s->d_cos;
@@ -798,7 +798,7 @@ RopeKvArgs rope_args(stage *s, int layer, int rows, const CallMeta *meta) {
 }
 
 // Prefill (T >= 2): projections on the matrix cores with bf16 hi/lo operand pairs.
-int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int T, const CallMeta *meta,
+int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int T, const RowMap &meta,
                       const float *x_src, float *x_dst) {
     const uint16_t *base = w.mha;
     const int H = s->H, F = s->F, qd = s->Hq * s->D;
@@ -870,7 +870,7 @@ int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int 
     return STAGE_OK;
 }
 
-AttnArgs decode_attn_args(stage *s, int layer, int rows, const CallMeta *meta, int grid_splits) {
+AttnArgs decode_attn_args(stage *s, int layer, int rows, const RowMap &meta, int grid_splits) {
     AttnArgs at{};
     at.q = s->ws_q;
     at.out = s->ws_attn;
@@ -902,7 +902,7 @@ bool decode_by_gemm(const stage *s, int rows) {
     const int qd = s->Hq * s->D;
     return rows > kGemvRows && s->H % 64 == 0 && s->F % 64 == 0 && qd % 64 == 0 && s->F >= s->H && qd >= s->H;
 }
-int run_layer_rows(stage *s, int layer, const LayerWeights &w, int rows, const CallMeta *meta, int grid_splits,
+int run_layer_rows(stage *s, int layer, const LayerWeights &w, int rows, const RowMap &meta, int grid_splits,
                    const float *x_src, float *x_dst, const TimeRec &rec) {
     const int H = s->H, F = s->F, qd = s->Hq * s->D;
     const size_t cap = gemv_part_floats(s);
@@ -951,7 +951,7 @@ int run_layer_rows(stage *s, int layer, const LayerWeights &w, int rows, const C
     return STAGE_OK;
 }
 
-int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int T, const CallMeta *meta,
+int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int T, const RowMap &meta,
                       int grid_splits, const float *x_src, float *x_dst) {
     if (T >= 2) return run_layer_prefill(s, layer, w, rows, T, meta, x_src, x_dst);
     if ((size_t)rows > s->part_rows || !s->ws_part_o || !s->ws_part_ml)
@@ -1193,7 +1193,8 @@ int run_call_body(stage *s, int n_mb, const int32_t *mb_ids, int B, int T, const
     const int grid_splits = (max_ctx + kDecodeSplitKeys - 1) / kDecodeSplitKeys;
     if (T == 1 && grid_splits > s->max_splits)
         return s->fail(STAGE_ESTATE, "attention partials hold %d splits, the call needs %d", s->max_splits, grid_splits);
-    HIP_TRY(launch_meta_write(meta, s->d_meta, s->cs));
+    const RowMap row_map{meta.n_seqs > 1 ? s->d_meta : nullptr, T, meta.seq_slot[0], meta.pos0[0]};
+    if (row_map.seqs) HIP_TRY(launch_meta_write(meta, s->d_meta, s->cs));
     s->calls++;
     if (decode) s->tok_decode += (long long)rows; else s->tok_prefill += (long long)rows;
 
@@ -1234,7 +1235,7 @@ int run_call_body(stage *s, int n_mb, const int32_t *mb_ids, int B, int T, const
                 if (!k.resident) s->bytes_direct += (long long)s->blk_bytes[b];
                 *base[b] = static_cast<const uint16_t *>(k.resident ? k.dev : k.host_dev);
             }
-            rc = run_layer(s, l, w, (int)rows, T, s->d_meta, grid_splits, src, x_out);
+            rc = run_layer(s, l, w, (int)rows, T, row_map, grid_splits, src, x_out);
             if (rc) return rc;
             continue;
         }
@@ -1253,7 +1254,7 @@ int run_call_body(stage *s, int n_mb, const int32_t *mb_ids, int B, int T, const
             if (check && (rc = check_slot_tag(s, sl, kMha, l, w.load, 0))) return rc;
         }
         if (!ly.blk[kMlp].resident) w.mlp_ready = s->slot_ready[kMlp][sl];
-        rc = run_layer(s, l, w, (int)rows, T, s->d_meta, grid_splits, src, x_out);
+        rc = run_layer(s, l, w, (int)rows, T, row_map, grid_splits, src, x_out);
         if (rc) return rc;
         // the layer's kernels are enqueued: its blocks must still hold it (no refill has begun)
         for (int b = 0; b < 2 && check; ++b)
