@@ -9,29 +9,29 @@
 
 namespace stg {
 
-// fp32 -> bf16 bits, round to nearest even (NaN kept quiet).
-__device__ __forceinline__ uint16_t pair_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) return (uint16_t)((u >> 16) | 0x40u);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+// The pairs of a (low half) and b (high half): two v_cvt_pk_bf16_f32 (nearest even, NaN kept quiet).
+__device__ __forceinline__ void split_pair2(float a, float b, uint32_t &hi, uint32_t &lo) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    hi = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+    lo = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)(a - __uint_as_float(hi << 16)),
+                                             (__bf16)(b - __uint_as_float(hi & 0xFFFF0000u))});
 }
 
 __device__ __forceinline__ void split_pair(float v, uint16_t &hi, uint16_t &lo) {
-    hi = pair_bf16(v);
-    lo = pair_bf16(v - __uint_as_float((uint32_t)hi << 16));
+    uint32_t h, l;
+    split_pair2(v, 0.f, h, l);
+    hi = (uint16_t)h;
+    lo = (uint16_t)l;
 }
 
 // The hi and lo of four consecutive elements of a 32-wide block (p: the first one's hi, 8-byte
 // aligned): two 8-byte stores, the lo 32 elements further.
 __device__ __forceinline__ void store_pair4(uint16_t *p, float4 v) {
-    uint16_t h[4], l[4];
-    split_pair(v.x, h[0], l[0]);
-    split_pair(v.y, h[1], l[1]);
-    split_pair(v.z, h[2], l[2]);
-    split_pair(v.w, h[3], l[3]);
-    *reinterpret_cast<uint2 *>(p) = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
-    *reinterpret_cast<uint2 *>(p + 32) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
+    uint2 h, l;
+    split_pair2(v.x, v.y, h.x, l.x);
+    split_pair2(v.z, v.w, h.y, l.y);
+    *reinterpret_cast<uint2 *>(p) = h;
+    *reinterpret_cast<uint2 *>(p + 32) = l;
 }
 
 }  // namespace stg
