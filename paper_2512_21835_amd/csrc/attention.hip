@@ -609,7 +609,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(AttnArgs a) {
     constexpr int ROW = 2 * D, CH = D / 8;                // bytes and 16-byte chunks of a key's row
     constexpr int TILE = KT * ROW, STAGE = 2 * TILE;      // K tile, then V tile
     constexpr int KPC = 1024 / ROW, CP = KT / KPC / 4;    // keys per copy; copies of K (and of V) per wavefront
-    __shared__ __align__(16) char lds[S * STAGE];
+    __shared__ __align__(256) char lds[S * STAGE];   // (whole rows: addresses are permuted by XOR)
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
