@@ -182,7 +182,7 @@ __device__ __forceinline__ void attn_decode_task(const AttnArgs &a, int split, i
             const float o_sum = ((sm.o[0][h][c] + sm.o[1][h][c]) + sm.o[2][h][c]) + sm.o[3][h][c];
             const float l_sum = ((sm.wl[0][h] + sm.wl[1][h]) + sm.wl[2][h]) + sm.wl[3][h];
             const int col = (g * G + h) * D + c;
-            if (a.out_pair) {
+            if (row < a.pair_rows) {
                 uint16_t *p = a.out_pair + row * a.out_pair_ld + pair_at(col);
                 split_pair(o_sum / l_sum, p[0], p[32]);
             } else {
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
     }
     const float4 v = make_float4(O.x / L, O.y / L, O.z / L, O.w / L);
     const int col = hq * D + 4 * cg;
-    if (a.out_pair) store_pair4(a.out_pair + row * a.out_pair_ld + pair_at(col), v);
+    if (row < a.pair_rows) store_pair4(a.out_pair + row * a.out_pair_ld + pair_at(col), v);
     else *reinterpret_cast<float4 *>(a.out + (size_t)row * hq_total * D + col) = v;
 }
 
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(256, UNITS == 1 ? 5 : 4) void attn_decode_mfma(Attn
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) {
                 const int col = (g * G + h) * D + 32 * wave + 16 * nb + l16;
-                if (a.out_pair) {
+                if (row < a.pair_rows) {
                     uint16_t *p = a.out_pair + row * a.out_pair_ld + pair_at(col);
                     split_pair(o[0][nb][i] / l_sum, p[0], p[32]);
                 } else {

@@ -583,17 +583,21 @@ void launch_rows(const GemvArgs &c, hipStream_t st, hipEvent_t e0, hipEvent_t e1
     }
 }
 
+// 16-unit blocks must not straddle the two halves of a RoPE head
+bool mfma_shape(int mode, int K, int head_dim) {
+    return K % kChunkK == 0 && (mode != GEMV_NORM_ROPE_KV || (head_dim / 2) % 16 == 0);
+}
+// Rows from which the matrix cores are faster (measured on the 8B- and 70B-shaped layers): 3, except
+// for square plain projections (the O projection), where the vector kernel keeps up to 4 rows.
+int mfma_min_rows(int mode, int N, int K) { return mode == GEMV_PLAIN_RESIDUAL && K <= N ? 5 : 3; }
+
 template <int MODE>
 hipError_t launch_mode(const GemvArgs &a, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-    // 16-unit blocks must not straddle the two halves of a RoPE head
-    const bool mfma_ok = a.K % kChunkK == 0 && (MODE != GEMV_NORM_ROPE_KV || (a.kv.head_dim / 2) % 16 == 0);
-    // rows from which the matrix cores are faster (measured on the 8B- and 70B-shaped layers):
-    // 3, except for square plain projections (the O projection), where the vector kernel keeps up
-    // to 4 rows
-    const int mfma_min_rows = MODE == GEMV_PLAIN_RESIDUAL && a.K <= a.N ? 5 : 3;
+    const bool mfma_ok = mfma_shape(MODE, a.K, a.kv.head_dim);
+    const int min_rows = mfma_min_rows(MODE, a.N, a.K);
     for (int r0 = 0, n = 0; r0 < a.rows; r0 += n) {
         const int left = a.rows - r0;
-        const bool mfma = mfma_ok && left >= mfma_min_rows;
+        const bool mfma = mfma_ok && left >= min_rows;
         n = min(left, mfma ? kMfmaRows : kMaxRowsPerLaunch);
         GemvArgs c = a;
         c.rows = n;
@@ -638,6 +642,12 @@ int device_compute_units() {
     }
     cached[dev].store(n, std::memory_order_relaxed);
     return n;
+}
+
+int gemv_fp32_rows(int mode, int rows, int N, int K, int head_dim) {
+    if (!mfma_shape(mode, K, head_dim)) return rows;
+    const int left = rows % kMfmaRows;
+    return left < mfma_min_rows(mode, N, K) ? left : 0;
 }
 
 hipError_t launch_gemv(int mode, GemvArgs a, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {

@@ -94,6 +94,9 @@ int device_compute_units();
 // launch (kernel timestamps, no extra stream packets).
 hipError_t launch_gemv(int mode, GemvArgs a, hipStream_t st, hipEvent_t ev_start = nullptr,
                        hipEvent_t ev_stop = nullptr);
+// Of a call of `rows` rows, how many (the last ones) launch_gemv multiplies with the activation in fp32,
+// on the vector kernel; the others' activation enters the matrix cores as a bf16 hi + lo pair.
+int gemv_fp32_rows(int mode, int rows, int N, int K, int head_dim);
 
 enum GemmMode { GEMM_STORE = 0, GEMM_RESIDUAL = 1, GEMM_SWIGLU = 2, GEMM_PARTIAL = 3 /* internal */ };
 
@@ -159,10 +162,12 @@ hipError_t launch_qkv(const GemmArgs &g, RopeKvArgs r, hipStream_t st);
 struct AttnArgs {
     const float *q;      // [rows, Hq d] rotated
     float *out;          // [rows, Hq d]
-    // when set, the output goes here instead of `out`, as the hi/lo pair the O projection GEMM reads
-    // ([rows, out_pair_ld], pair_at layout)
+    // the output of rows below pair_rows goes here instead of `out`, as the hi/lo pair the O projection
+    // GEMM reads ([rows, out_pair_ld], pair_at layout; out_pair_ld = Hq d elements, the bytes of a row of
+    // `out`, so both may be the same memory)
     uint16_t *out_pair;
     long out_pair_ld;
+    int pair_rows;
     float *part_o;       // [rows, Hq, max_splits, d] unnormalised partial outputs
     float *part_ml;      // [rows, Hq, max_splits, 2] partial max and sum
     KvView kv;

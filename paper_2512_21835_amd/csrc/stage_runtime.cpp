@@ -826,6 +826,7 @@ int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int 
     at.meta = meta;
     at.out_pair = s->ws_pair;   // the O projection's operand pair
     at.out_pair_ld = pair_ld(qd);
+    at.pair_rows = rows;
     HIP_TRY(launch_attention(at, s->cs));
 
     GemmArgs o{};
@@ -889,18 +890,96 @@ AttnArgs decode_attn_args(stage *s, int layer, int rows, const RowMap &meta, int
     return at;
 }
 
+// The decode GEMVs of a layer for the rows `first` .. `first` + `rows` - 1 of a call.
+struct LayerGemvs {
+    GemvArgs q{}, o{}, gu{}, dn{};
+};
+LayerGemvs layer_gemvs(stage *s, int layer, const LayerWeights &w, int first, int rows, const RowMap &meta,
+                       const float *x_src, float *x_dst) {
+    LayerGemvs g;
+    const size_t H = s->H, F = s->F, qd = (size_t)s->Hq * s->D, at = first;
+    g.q.w = w.mha + s->off_wqkv / 2;
+    g.q.act = x_src + at * H;
+    g.q.act_ld = s->H;
+    g.q.gain = w.mha + s->off_g1 / 2;
+    g.q.out = s->ws_q + at * qd;
+    g.q.out_ld = (long)qd;
+    g.q.N = s->qkv_rows;
+    g.q.K = s->H;
+    g.q.row0 = first;
+    g.q.eps = s->cfg.rms_eps;
+    g.q.cos_t = s->d_cos;
+    g.q.sin_t = s->d_sin;
+    g.q.kv = kv_view(s, layer);
+    g.q.n_q_heads = s->Hq;
+    g.q.kv_fp32 = s->cfg.kv_fp32;
+    g.q.meta = meta;
+
+    g.o.w = w.mha + s->off_wo / 2;
+    g.o.act = s->ws_attn + at * qd;
+    g.o.act_ld = (long)qd;
+    g.o.res = x_src + at * H;
+    g.o.out = x_dst + at * H;
+    g.o.out_ld = s->H;
+    g.o.N = s->H;
+    g.o.K = (int)qd;
+
+    g.gu.w = w.mlp + s->off_wg / 2;
+    g.gu.w2 = w.mlp + s->off_wu / 2;
+    g.gu.act = x_dst + at * H;
+    g.gu.act_ld = s->H;
+    g.gu.gain = w.mlp + s->off_g2 / 2;
+    g.gu.out = s->ws_h + at * F;
+    g.gu.out_ld = s->F;
+    g.gu.N = s->F;
+    g.gu.K = s->H;
+    g.gu.eps = s->cfg.rms_eps;
+
+    g.dn.w = w.mlp + s->off_wd / 2;
+    g.dn.act = s->ws_h + at * F;
+    g.dn.act_ld = s->F;
+    g.dn.res = x_dst + at * H;
+    g.dn.out = x_dst + at * H;
+    g.dn.out_ld = s->H;
+    g.dn.N = s->H;
+    g.dn.K = s->F;
+    for (GemvArgs *a : {&g.q, &g.o, &g.gu, &g.dn}) {
+        a->rows = rows;
+        a->split_part = s->ws_split;  // matrix-core launches may split K
+        a->split_ss = s->ws_split_ss;
+    }
+    return g;
+}
+
 // One token for each of more sequences than a decode GEMV takes at once (16): the GEMVs would read
 // the weights again for every 16 rows, so the projections run as GEMMs on operand pairs, which read
 // them once for all rows (up to 64).  Two 8B-shaped layers, 64 rows at about 830 tokens: 953 -> 380 us
-// (a layer's projections 420 -> 125 us).  At 17 rows one pass over each weight replaces two; up to 16
-// the GEMVs stay, which stream the weights faster (6.5 against 5.4 TB/s) and need no pair passes.
+// (a layer's projections 420 -> 125 us).  Up to 16 rows the GEMVs stay, which stream the weights faster
+// (6.5 against 5.4 TB/s) and need no pair passes.
+//
+// What the GEMVs multiply in fp32, the last one or two rows (four of a square O projection) past a
+// multiple of 16, keeps that: those rows run on the vector GEMV beside the GEMM of the others.  On pairs
+// the error of such a row, 8B-shaped layer over an fp32 cache, is 4.2e-6 of it against 2.6e-7.  Widths off
+// 128 run in fp32 throughout there, so they stay on the GEMVs, and so does a call with 16 rows or fewer
+// left for the GEMM.
 // The pairs take no memory of their own (stage_decode_noalloc has none to give): the normalised
 // input's lies in ws_h and later ws_q, the attention output's in ws_attn, that of the SwiGLU output
-// in ws_h.  The shape has to leave room for that, and whole 64-wide k tiles.
+// in ws_h; a row's pair is as long as its fp32 values, which the GEMV rows keep there.  The shape has to
+// leave room for that.
 constexpr int kGemvRows = 16;
-bool decode_by_gemm(const stage *s, int rows) {
+struct Fp32Rows {
+    int qkv, o, mlp;   // of a call's last rows, those on the GEMVs (mlp: gate/up, whose output down reads)
+};
+Fp32Rows fp32_rows(const stage *s, int rows) {
     const int qd = s->Hq * s->D;
-    return rows > kGemvRows && s->H % 64 == 0 && s->F % 64 == 0 && qd % 64 == 0 && s->F >= s->H && qd >= s->H;
+    return {gemv_fp32_rows(GEMV_NORM_ROPE_KV, rows, s->qkv_rows, s->H, s->D),
+            gemv_fp32_rows(GEMV_PLAIN_RESIDUAL, rows, s->H, qd, s->D),
+            std::max(gemv_fp32_rows(GEMV_NORM_SWIGLU, rows, s->F, s->H, s->D),
+                     gemv_fp32_rows(GEMV_PLAIN_RESIDUAL, rows, s->H, s->F, s->D))};
+}
+bool decode_by_gemm(const stage *s, int rows) {
+    const Fp32Rows v = fp32_rows(s, rows);
+    return rows - std::max(v.qkv, v.mlp) > kGemvRows && rows > v.o && s->F >= s->H && s->Hq * s->D >= s->H;
 }
 int run_layer_rows(stage *s, int layer, const LayerWeights &w, int rows, const RowMap &meta, int grid_splits,
                    const float *x_src, float *x_dst, const TimeRec &rec) {
@@ -908,46 +987,55 @@ int run_layer_rows(stage *s, int layer, const LayerWeights &w, int rows, const R
     const size_t cap = gemv_part_floats(s);
     uint16_t *const h = reinterpret_cast<uint16_t *>(s->ws_h), *const att = reinterpret_cast<uint16_t *>(s->ws_attn);
     uint16_t *const y2 = reinterpret_cast<uint16_t *>(s->ws_q);
+    const Fp32Rows v = fp32_rows(s, rows);
+    const int n_q = rows - v.qkv, n_o = rows - v.o, n_mlp = rows - v.mlp;   // rows of the GEMMs
+    auto gemvs = [&](int first) { return layer_gemvs(s, layer, w, first, rows - first, meta, x_src, x_dst); };
 
-    HIP_TRY(launch_rmsnorm_split(x_src, w.mha + s->off_g1 / 2, s->cfg.rms_eps, rows, H, h, pair_ld(H), s->cs));
+    HIP_TRY(launch_rmsnorm_split(x_src, w.mha + s->off_g1 / 2, s->cfg.rms_eps, n_q, H, h, pair_ld(H), s->cs));
     GemmArgs q{};
     q.a = h; q.lda = pair_ld(H);
     q.w[0] = w.mha + s->off_wqkv / 2;
     q.out = s->ws_split; q.ldo = s->qkv_rows;
-    q.M = rows; q.N = s->qkv_rows; q.K = H;
+    q.M = n_q; q.N = s->qkv_rows; q.K = H;
     q.part = s->ws_split; q.part_cap64 = cap;
-    HIP_TRY(launch_qkv(q, rope_args(s, layer, rows, meta), s->cs));
+    HIP_TRY(launch_qkv(q, rope_args(s, layer, n_q, meta), s->cs));
+    HIP_TRY(launch_gemv(GEMV_NORM_ROPE_KV, gemvs(n_q).q, s->cs));
     AttnArgs at = decode_attn_args(s, layer, rows, meta, grid_splits);
     at.out_pair = att;
     at.out_pair_ld = pair_ld(qd);
+    at.pair_rows = n_o;
     HIP_TRY(launch_attention(at, s->cs));
     GemmArgs o{};
     o.a = att; o.lda = pair_ld(qd);
     o.w[0] = w.mha + s->off_wo / 2;
     o.out = x_dst; o.res = x_src; o.ldo = H;
-    o.M = rows; o.N = H; o.K = qd;
+    o.M = n_o; o.N = H; o.K = qd;
     o.part = s->ws_split; o.part_cap64 = cap;
     HIP_TRY(launch_gemm(GEMM_RESIDUAL, o, 1, s->cs));
+    HIP_TRY(launch_gemv(GEMV_PLAIN_RESIDUAL, gemvs(n_o).o, s->cs));
 
     int rc = mlp_boundary(s, layer, w);
     if (rc) return rc;
-    HIP_TRY(launch_rmsnorm_split(x_dst, w.mlp + s->off_g2 / 2, s->cfg.rms_eps, rows, H, y2, pair_ld(H), s->cs));
+    HIP_TRY(launch_rmsnorm_split(x_dst, w.mlp + s->off_g2 / 2, s->cfg.rms_eps, n_mlp, H, y2, pair_ld(H), s->cs));
     GemmArgs gu{};
     gu.a = y2; gu.lda = pair_ld(H);
     gu.w[0] = w.mlp + s->off_wg / 2;
     gu.w[1] = w.mlp + s->off_wu / 2;
-    gu.M = rows; gu.N = F; gu.K = H;
+    gu.M = n_mlp; gu.N = F; gu.K = H;
     gu.out_pair = h; gu.ldo = pair_ld(F);
+    const LayerGemvs rest = gemvs(n_mlp);
     if (rec.a) HIP_TRY(hipEventRecord(rec.a, s->cs));
     HIP_TRY(launch_gemm(GEMM_SWIGLU, gu, 1, s->cs));
+    HIP_TRY(launch_gemv(GEMV_NORM_SWIGLU, rest.gu, s->cs));
     if (rec.b) HIP_TRY(hipEventRecord(rec.b, s->cs));
     GemmArgs dn{};
     dn.a = h; dn.lda = pair_ld(F);
     dn.w[0] = w.mlp + s->off_wd / 2;
     dn.out = x_dst; dn.res = x_dst; dn.ldo = H;
-    dn.M = rows; dn.N = H; dn.K = F;
+    dn.M = n_mlp; dn.N = H; dn.K = F;
     dn.part = s->ws_split; dn.part_cap64 = cap;
     HIP_TRY(launch_gemm(GEMM_RESIDUAL, dn, 1, s->cs));
+    HIP_TRY(launch_gemv(GEMV_PLAIN_RESIDUAL, rest.dn, s->cs));
     return STAGE_OK;
 }
 
@@ -969,79 +1057,14 @@ int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int 
         if (rc == STAGE_OK && rec.a) s->recs.push_back(rec);
         return rc;
     }
-    const uint16_t *base = w.mha, *mlp = w.mlp;
-    const size_t qd = (size_t)s->Hq * s->D;
-
-    GemvArgs q{};
-    q.w = base + s->off_wqkv / 2;
-    q.act = x_src;
-    q.act_ld = s->H;
-    q.gain = base + s->off_g1 / 2;
-    q.out = s->ws_q;
-    q.out_ld = (long)qd;
-    q.N = s->qkv_rows;
-    q.K = s->H;
-    q.rows = rows;
-    q.eps = s->cfg.rms_eps;
-    q.cos_t = s->d_cos;
-    q.sin_t = s->d_sin;
-    q.kv = kv_view(s, layer);
-    q.n_q_heads = s->Hq;
-    q.kv_fp32 = s->cfg.kv_fp32;
-    q.meta = meta;
-    q.split_part = s->ws_split;  // matrix-core launches may split K
-    q.split_ss = s->ws_split_ss;
-
-    const AttnArgs at = decode_attn_args(s, layer, rows, meta, grid_splits);
-
-    GemvArgs o{};
-    o.w = base + s->off_wo / 2;
-    o.act = s->ws_attn;
-    o.act_ld = (long)qd;
-    o.res = x_src;
-    o.out = x_dst;
-    o.out_ld = s->H;
-    o.N = s->H;
-    o.K = (int)qd;
-    o.rows = rows;
-    o.split_part = s->ws_split;
-    o.split_ss = s->ws_split_ss;
-
-    GemvArgs gu{};
-    gu.w = mlp + s->off_wg / 2;
-    gu.w2 = mlp + s->off_wu / 2;
-    gu.act = x_dst;
-    gu.act_ld = s->H;
-    gu.gain = mlp + s->off_g2 / 2;
-    gu.out = s->ws_h;
-    gu.out_ld = s->F;
-    gu.N = s->F;
-    gu.K = s->H;
-    gu.rows = rows;
-    gu.eps = s->cfg.rms_eps;
-    gu.split_part = s->ws_split;
-    gu.split_ss = s->ws_split_ss;
-
-    GemvArgs dn{};
-    dn.w = mlp + s->off_wd / 2;
-    dn.act = s->ws_h;
-    dn.act_ld = s->F;
-    dn.res = x_dst;
-    dn.out = x_dst;
-    dn.out_ld = s->H;
-    dn.N = s->H;
-    dn.K = s->F;
-    dn.rows = rows;
-    dn.split_part = s->ws_split;
-    dn.split_ss = s->ws_split_ss;
-
-    HIP_TRY(launch_gemv(GEMV_NORM_ROPE_KV, q, s->cs));
-    HIP_TRY(launch_attention(at, s->cs));
-    HIP_TRY(launch_gemv(GEMV_PLAIN_RESIDUAL, o, s->cs));
+    const LayerGemvs g = layer_gemvs(s, layer, w, 0, rows, meta, x_src, x_dst);
+    HIP_TRY(launch_gemv(GEMV_NORM_ROPE_KV, g.q, s->cs));
+    HIP_TRY(launch_attention(decode_attn_args(s, layer, rows, meta, grid_splits), s->cs));
+    HIP_TRY(launch_gemv(GEMV_PLAIN_RESIDUAL, g.o, s->cs));
     int rc = mlp_boundary(s, layer, w);
     if (rc) return rc;
-    HIP_TRY(launch_gemv(GEMV_NORM_SWIGLU, gu, s->cs, rec.a, rec.b));
-    HIP_TRY(launch_gemv(GEMV_PLAIN_RESIDUAL, dn, s->cs));
+    HIP_TRY(launch_gemv(GEMV_NORM_SWIGLU, g.gu, s->cs, rec.a, rec.b));
+    HIP_TRY(launch_gemv(GEMV_PLAIN_RESIDUAL, g.dn, s->cs));
     if (rec.a) s->recs.push_back(rec);
     return STAGE_OK;
 }

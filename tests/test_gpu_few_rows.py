@@ -114,3 +114,67 @@ def test_noalloc_and_host_weights_give_the_same_rows(zero_copy):
     got = run(not zero_copy, P.stage_decode if zero_copy else P.stage_decode_noalloc)
     for a, b in zip(want, got):
         assert np.array_equal(a, b)
+
+
+def _decode_calls(shape, w, rows, calls):
+    """One decode step of each of `rows` sequences (fp32 cache; 40 to 70 tokens held), as `calls` group them."""
+    import torch
+    import paper_2512_21835_amd as P
+
+    x = torch.from_numpy(synth.normal_f32(synth.seed_of(0xF3, 1), (rows, shape.hidden)))
+    kv = [torch.from_numpy(synth.normal_f32(synth.seed_of(0xF3, i), (1, 70, shape.n_kv_heads, shape.head_dim))) for i in (2, 3)]
+    with compute_stream() as cs:
+        cfg = P.config_for(shape, max_microbatches=rows, max_batch=1, max_context=80, n_resident_max=1, kv_fp32=True,
+                           compute_stream=cs.handle)
+        h = P.stage_init(cfg)
+        try:
+            P.stage_load_layer(h, 0, w, 1)
+            for m in range(rows):
+                n = 40 + 7 * m % 31
+                P.stage_kv_append(h, m, 0, n, *(t[:, :n].contiguous() for t in kv))
+            y = {}
+            for ids in calls:
+                xd = x[ids].cuda()
+                yd = torch.empty_like(xd)
+                torch.cuda.synchronize()
+                P.stage_decode(h, ids, 1, xd, yd)
+                P.stage_sync(h)
+                y.update(zip(ids, yd.cpu().numpy()))
+            return y
+        finally:
+            P.stage_destroy(h)
+
+
+# Widths off 128, and an ffn as wide as the hidden size (whose down projection keeps four rows in fp32).
+OFF_128 = synth.StageShape("fp32-rows-1L-h192", 75, 1, 192, 3, 3, 64, 320)
+SQUARE = synth.StageShape("fp32-rows-1L-h512", 76, 1, 512, 4, 2, 128, 512)
+
+
+@pytest.mark.parametrize("shape,rows,last", [(CUT_2_2_8, 17, 1), (CUT_2_2_8, 18, 2), (CUT_2_2_8, 33, 1), (CUT_2_2_8, 50, 2),
+                                             (SQUARE, 34, 2), (OFF_128, 18, 18), (OFF_128, 33, 33)],
+                         ids=lambda p: getattr(p, "name", p))
+def test_rows_that_run_in_fp32(shape, rows, last):
+    """The rows past a multiple of 16 that the decode GEMVs multiply in fp32 keep their bits (those of the
+    row alone) in calls whose other rows run as GEMMs on 16-bit pairs; so does every row of widths off 128."""
+    _gpu()
+    w = weights_of(shape)(0)
+    ids = list(range(rows - last, rows))
+    together = _decode_calls(shape, w, rows, [list(range(rows))])
+    alone = _decode_calls(shape, w, rows, [[i] for i in ids])
+    for i in ids:
+        assert np.array_equal(together[i], alone[i]), i
+
+
+@pytest.mark.parametrize("rows", [19, 20, 35, 36])
+def test_square_o_projection_rows_in_fp32(rows):
+    """A square O projection keeps the last three and four rows in fp32 as well, the others of their layer on
+    pairs: with zero Q, K, V and gate weights the O projection's is the only product that counts."""
+    _gpu()
+    w = dict(weights_of(CUT_2_2_8)(0))
+    for t in ("wq", "wk", "wv", "wg"):
+        w[t] = np.zeros_like(w[t])
+    ids = list(range(16 * (rows // 16), rows))
+    together = _decode_calls(CUT_2_2_8, w, rows, [list(range(rows))])
+    alone = _decode_calls(CUT_2_2_8, w, rows, [[i] for i in ids])
+    for i in ids:
+        assert np.array_equal(together[i], alone[i]), i
