@@ -811,23 +811,15 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(AttnArgs a) {
     if (!qvalid) return;
     // O^T[d = 32 b + 8 (i / 4) + 4 half + i % 4][query col]
     const float inv = 1.f / l_run;
-    if (a.out_pair) {   // four consecutive d of one 32-wide block per store
-        uint16_t *prow = a.out_pair + qrow * a.out_pair_ld;
-        const int k0 = (g * G + hh) * D;
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                store_pair4(prow + pair_at(k0 + 32 * b + 8 * j + 4 * half),
-                            make_float4(o[b][4 * j] * inv, o[b][4 * j + 1] * inv, o[b][4 * j + 2] * inv,
-                                        o[b][4 * j + 3] * inv));
-        return;
-    }
-    float *orow = a.out + qrow * q_ld + (size_t)(g * G + hh) * D;
+    uint16_t *prow = a.out_pair + qrow * a.out_pair_ld;   // four consecutive d of one 32-wide block per store
+    const int k0 = (g * G + hh) * D;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) orow[32 * b + 8 * (i / 4) + 4 * half + (i % 4)] = o[b][i] * inv;
+        for (int j = 0; j < 4; ++j)
+            store_pair4(prow + pair_at(k0 + 32 * b + 8 * j + 4 * half),
+                        make_float4(o[b][4 * j] * inv, o[b][4 * j + 1] * inv, o[b][4 * j + 2] * inv,
+                                    o[b][4 * j + 3] * inv));
 }
 
 // Prefill attention over an fp32 cache, in fp32 throughout, on v_mfma_f32_32x32x2_f32 (fp32 operands,
@@ -1023,10 +1015,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
                 if (both) v[x] = fmaf(st[64 * (16 * b + i)], w1, v[x]);
                 v[x] /= l;
             }
-            const int c = k0 + 32 * b + 8 * j + 4 * half;
-            const float4 v4 = make_float4(v[0], v[1], v[2], v[3]);
-            if (a.out_pair) store_pair4(a.out_pair + qrow * a.out_pair_ld + pair_at(c), v4);
-            else *reinterpret_cast<float4 *>(a.out + qrow * q_ld + c) = v4;
+            store_pair4(a.out_pair + qrow * a.out_pair_ld + pair_at(k0 + 32 * b + 8 * j + 4 * half),
+                        make_float4(v[0], v[1], v[2], v[3]));
         }
 }
 
@@ -1034,7 +1024,7 @@ template <int G, int D>
 hipError_t launch_gd(const AttnArgs &a, hipStream_t st) {
     const int hkv = a.kv.n_kv_heads;
     if (a.split_keys == 0) {
-        if (a.n_seqs * a.rows_per_seq != a.rows) return hipErrorInvalidValue;
+        if (a.n_seqs * a.rows_per_seq != a.rows || a.pair_rows != a.rows) return hipErrorInvalidValue;
         if (a.kv_fp32) {
             constexpr int BQ = 64 / G;
             dim3 grid(hkv, a.n_seqs, (a.rows_per_seq + BQ - 1) / BQ);

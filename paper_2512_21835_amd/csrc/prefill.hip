@@ -692,11 +692,11 @@ void launch_part_residual(const GemmArgs &a, hipStream_t st) {
 
 }  // namespace
 
-size_t gemm_part_floats(int rows, int N, int K, size_t cap64) {
-    size_t most = 0;
-    for (int m = 1; m <= min(rows, kFewRows); ++m) {
-        const int parts = gemm_plan(m, N, K, false, true, cap64).parts();
-        if (parts > 1) most = max(most, (size_t)parts * m * N);
+size_t gemm_part_floats(int rows, int N, int K, size_t cap64, size_t most) {
+    for (int m = min(rows, kFewRows); m >= 1; --m) {
+        const GemmPlan p = gemm_plan(m, N, K, false, true, cap64);
+        if (p.ranges == 1 || (size_t)p.ranges * m * N <= most) break;   // (the cut is the same for every m)
+        if (p.parts() > 1) most = max(most, (size_t)p.parts() * m * N);
     }
     return most;
 }

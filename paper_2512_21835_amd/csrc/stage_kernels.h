@@ -134,9 +134,9 @@ hipError_t launch_gemm(int mode, const GemmArgs &a, int n_mats, hipStream_t st);
 // the partial products are always added in the same order, so a row's result is the same for any
 // number of rows up to kFewRows (and the same for any number beyond, where K is whole).
 constexpr int kFewRows = 1024;
-// Floats of GemmArgs::part that no call of up to `rows` rows exceeds for a matrix [N, K], and the
-// most that the cut assumes for up to 64 rows (it takes fewer ranges where they would not fit).
-size_t gemm_part_floats(int rows, int N, int K, size_t cap64);
+// Floats of GemmArgs::part that no call of up to `rows` rows exceeds for a matrix [N, K], or `most` if that
+// is more.  cap64: what the cut assumes for up to 64 rows (it takes fewer ranges where they would not fit).
+size_t gemm_part_floats(int rows, int N, int K, size_t cap64, size_t most);
 // y = rmsnorm(x) * g as a pair [rows, H] (row stride ld).
 hipError_t launch_rmsnorm_split(const float *x, const uint16_t *g, float eps, int rows, int H, uint16_t *pair,
                                 long ld, hipStream_t st);
@@ -161,7 +161,7 @@ hipError_t launch_qkv(const GemmArgs &g, RopeKvArgs r, hipStream_t st);
 
 struct AttnArgs {
     const float *q;      // [rows, Hq d] rotated
-    float *out;          // [rows, Hq d]
+    float *out;          // [rows, Hq d] (prefill: every row goes to out_pair)
     // the output of rows below pair_rows goes here instead of `out`, as the hi/lo pair the O projection
     // GEMM reads ([rows, out_pair_ld], pair_at layout; out_pair_ld = Hq d elements, the bytes of a row of
     // `out`, so both may be the same memory)

@@ -109,6 +109,7 @@ struct LaneState {
     uint16_t *ws_pair = nullptr;
     float *ws_part_o = nullptr, *ws_part_ml = nullptr;
     float *ws_split = nullptr, *ws_split_ss = nullptr;
+    size_t split_floats = 0;
 };
 
 struct stage {
@@ -152,6 +153,7 @@ struct stage {
     int max_splits = 0;
     float *ws_part_o = nullptr, *ws_part_ml = nullptr;
     float *ws_split = nullptr, *ws_split_ss = nullptr;  // partial products of projections cut in K
+    size_t split_floats = 0;                            // of ws_split
     void *ws_dense = nullptr;
     size_t ws_dense_bytes = 0;
 
@@ -275,6 +277,7 @@ void swap_workspaces(stage *s, LaneState &o) {
     std::swap(s->ws_part_ml, o.ws_part_ml);
     std::swap(s->ws_split, o.ws_split);
     std::swap(s->ws_split_ss, o.ws_split_ss);
+    std::swap(s->split_floats, o.split_floats);
 }
 
 // Exchanges the stage's call state (lane 0's, or the lane swapped in) with lanes[l]'s.
@@ -492,17 +495,19 @@ int set_residency(stage *s, int layer, int code) {
     return STAGE_OK;
 }
 
-// Floats of the partial products of a call's projections: the decode GEMVs' (and what a GEMM of up
-// to 64 rows may use of them), and with them those of the GEMMs of up to kFewRows rows.
+// Floats of the partial products of a call's projections: those of the decode GEMVs and of GEMMs of up
+// to 64 rows, which every lane has from the start; and of calls of up to `rows` rows, for which the
+// workspace grows with the others (1024 rows: 101 MB at 8B width, 126 at 70B, against 15 and 29).
 size_t gemv_part_floats(const stage *s) {
     return (size_t)kGemvMaxSplits * 2 * 16 * std::max<size_t>(std::max<size_t>(s->qkv_rows / 2, s->H), s->F);
 }
-size_t part_floats(const stage *s) {
+size_t part_floats(const stage *s, size_t rows) {
     const size_t cap = gemv_part_floats(s);
-    const int qd = s->Hq * s->D;
+    const int qd = s->Hq * s->D, cut_rows = (int)std::min<size_t>(rows, kFewRows);
     size_t n = cap;
-    for (const auto &[N, K] : {std::pair{s->qkv_rows, s->H}, {s->H, qd}, {s->H, s->F}})
-        n = std::max(n, gemm_part_floats(kFewRows, N, K, cap));
+    if (rows > 64)
+        for (const auto &[N, K] : {std::pair{s->H, s->F}, {s->qkv_rows, s->H}, {s->H, qd}})
+            n = gemm_part_floats(cut_rows, N, K, cap, n);
     return n;
 }
 
@@ -518,17 +523,30 @@ int ensure_workspace(stage *s, size_t rows, bool split_attention) {
         s->ws_pair = nullptr;
         s->ws_rows = 0;
         const size_t qd = (size_t)s->Hq * s->D;
-        // ws_qkv holds the prefill QKV rows, the gate and up halves side by side, or the pair of h
-        const size_t wide = std::max<size_t>(std::max<size_t>(s->qkv_rows, 2 * (size_t)s->F),
+        // ws_qkv holds the prefill QKV rows, the pair of h, or (widths off 32) the gate and up halves side
+        // by side; ws_attn and ws_h belong to calls of one token per sequence
+        const size_t wide = std::max<size_t>(std::max<size_t>(s->qkv_rows, s->H % 32 ? 2 * (size_t)s->F : 0),
                                              (size_t)pair_ld(s->F) / 2);
+        const size_t seqs = std::min<size_t>(rows, kMaxSeqs);
         const size_t pair = (size_t)pair_ld(std::max<size_t>(std::max<size_t>(s->H, qd), s->F));
         if (hipMalloc(&s->ws_qkv, rows * wide * sizeof(float)) != hipSuccess ||
             hipMalloc(&s->ws_pair, rows * pair * sizeof(uint16_t)) != hipSuccess ||
             hipMalloc(&s->ws_q, rows * qd * sizeof(float)) != hipSuccess ||
-            hipMalloc(&s->ws_attn, rows * qd * sizeof(float)) != hipSuccess ||
-            hipMalloc(&s->ws_h, rows * (size_t)s->F * sizeof(float)) != hipSuccess) {
+            hipMalloc(&s->ws_attn, seqs * qd * sizeof(float)) != hipSuccess ||
+            hipMalloc(&s->ws_h, seqs * (size_t)s->F * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             return s->fail(STAGE_ENOMEM, "workspace for %zu rows does not fit", rows);
+        }
+        const size_t split = part_floats(s, rows);
+        if (split > s->split_floats) {   // (decode calls need the old one: it stays if there is no room)
+            float *grown = nullptr;
+            if (hipMalloc(&grown, split * sizeof(float)) != hipSuccess) {
+                (void)hipGetLastError();
+                return s->fail(STAGE_ENOMEM, "workspace for %zu rows does not fit", rows);
+            }
+            (void)hipFree(s->ws_split);
+            s->ws_split = grown;
+            s->split_floats = split;
         }
         s->ws_rows = rows;
     }
@@ -815,7 +833,6 @@ int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int 
 
     AttnArgs at{};
     at.q = s->ws_q;
-    at.out = s->ws_attn;
     at.kv = kv_view(s, layer);
     at.n_q_heads = s->Hq;
     at.kv_fp32 = s->cfg.kv_fp32;
@@ -1441,11 +1458,12 @@ int stage_init(const stage_config *cfg, stage **out) {
         hipMalloc(&s->d_cos, sizeof(float) * (size_t)c.max_context * (s->D / 2)) != hipSuccess ||
         hipMalloc(&s->d_sin, sizeof(float) * (size_t)c.max_context * (s->D / 2)) != hipSuccess ||
         hipMalloc(&s->d_meta, sizeof(CallMeta)) != hipSuccess ||
-        hipMalloc(&s->ws_split, sizeof(float) * part_floats(s)) != hipSuccess ||
+        hipMalloc(&s->ws_split, sizeof(float) * gemv_part_floats(s)) != hipSuccess ||
         hipMalloc(&s->ws_split_ss, sizeof(float) * kGemvMaxSplits * 16) != hipSuccess) {
         (void)hipGetLastError();
         return cleanup(STAGE_ENOMEM);
     }
+    s->split_floats = gemv_part_floats(s);
     s->block_park.assign(s->n_blocks, nullptr);
     if (hipMemsetAsync(s->d_table, 0, sizeof(int) * (size_t)s->n_seq_slots * s->max_blocks, s->cs) != hipSuccess)
         return cleanup(STAGE_EHIP);
@@ -1457,11 +1475,12 @@ int stage_init(const stage_config *cfg, stage **out) {
             else if (create_private_stream(c.device, &ln.cs) == hipSuccess) ln.own_cs = true;
             else return cleanup(STAGE_EHIP);
             if (hipMalloc(&ln.d_meta, sizeof(CallMeta)) != hipSuccess ||
-                hipMalloc(&ln.ws_split, sizeof(float) * part_floats(s)) != hipSuccess ||
+                hipMalloc(&ln.ws_split, sizeof(float) * gemv_part_floats(s)) != hipSuccess ||
                 hipMalloc(&ln.ws_split_ss, sizeof(float) * kGemvMaxSplits * 16) != hipSuccess) {
                 (void)hipGetLastError();
                 return cleanup(STAGE_ENOMEM);
             }
+            ln.split_floats = gemv_part_floats(s);
         }
         s->seq_stream.assign(s->n_seq_slots, nullptr);
         s->seq_ev.assign(s->n_seq_slots, nullptr);
