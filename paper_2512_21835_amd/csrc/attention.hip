@@ -956,7 +956,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) o[b][i] *= alpha;
         }
-        if (careful) {   // key by key, hidden keys left out
+        if (careful) {   // key by key, hidden keys left out; in the order of the MFMAs' sums: the same bits
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const float other = lane_xor(s[i], 32);

@@ -22,14 +22,15 @@ def test_calls_around_the_tiles(g, d):
         assert 1 - m["cos"] <= 5e-9 and m["max_abs"] <= 5e-4 * m["rms_ref"], (name, m)
 
 
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
-def test_a_later_token_that_is_not_finite(bad):
-    """Rows before a token whose K and V are not finite keep their values."""
+def test_a_later_token_that_is_not_finite(bad, d):
+    """Rows before a token whose K and V are not finite keep their bits; the rows that see it are not finite."""
     _gpu()
     import torch
     import paper_2512_21835_amd as P
 
-    shape, n, at = synth.StageShape("f32-nan", 299, 1, 256, 4, 2, 64, 512), 70, 40
+    shape, n, at = synth.StageShape(f"f32-nan-d{d}", 235 + d, 1, 256, 4, 2, d, 512), 70, 40
     w = weights_of(shape)(0)
     x = torch.from_numpy(synth.normal_f32(synth.seed_of(0xF7, 1), (1, 1, n, shape.hidden)))
     spoilt = x.clone()
@@ -50,6 +51,6 @@ def test_a_later_token_that_is_not_finite(bad):
                 out.append(yd.cpu().numpy()[0, 0])
         finally:
             P.stage_destroy(h)
-    # key by key or in pairs of keys: two orders of the same fp32 sums
-    assert np.abs(out[0][:at] - out[1][:at]).max() <= 1e-5 * np.abs(out[0]).max()
+    # (key by key adds in the order in which the matrix instruction takes its two keys)
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0][:at], out[1][:at])
     assert not np.isfinite(out[1][at:]).all(1).any()
