@@ -375,6 +375,23 @@ def compare(got: np.ndarray, ref: np.ndarray, x_got: np.ndarray, x_ref: np.ndarr
             "worst_ref": float(r.flat[worst])}
 
 
+# What fp32 sums and 16-bit operand pairs (2^-17 per factor) leave over an fp32 cache, about four times the
+# largest seen against float64: 2-norm and largest element, relative to the rows.  An operand that lost its lo
+# half (2^-9 per factor) is outside, whichever projection it feeds (test_fp32_bound_cpu).
+FP32_REL, FP32_MAX = 5e-5, 3e-4
+
+
+def fp32_errors(got: np.ndarray, ref: np.ndarray) -> Tuple[float, float]:
+    r = ref.astype(np.float64)
+    d = got.astype(np.float64) - r
+    return float(np.linalg.norm(d) / np.linalg.norm(r)), float(np.abs(d).max() / np.sqrt((r * r).mean()))
+
+
+def fp32_close(got: np.ndarray, ref: np.ndarray) -> bool:
+    rel, most = fp32_errors(got, ref)
+    return rel <= FP32_REL and most <= FP32_MAX
+
+
 def row_origin(sc: Scenario, row: int) -> Tuple[int, str, int, int, int]:
     """Where flat output row `row` of a run of the scenario comes from: (call index, kind, mb, b,
     position in the sequence); rows are in call order, each call's rows [mb][b][t]."""

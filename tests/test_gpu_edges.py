@@ -215,18 +215,21 @@ def test_single_split_rows_give_the_merged_bits(shape_name, kv_fp32):
         assert np.array_equal(alone[step][0], mixed[step][0]), f"step {step}"
 
 
-# One narrow layer whose prefill gate/up GEMM (M = 2000 rows, 2F = 8000 gate/up rows: ragged in both
-# dimensions) still fills the GPU with 256 x 256 tiles, over K = 64 or 96: the software-pipelined k
-# loop with two tiles (only its peeled tail) and with three (one pass of the loop body).
-NARROW_H64 = synth.StageShape("narrow-1L-h64", 3, 1, 64, 1, 1, 64, 4000)
-NARROW_H96 = synth.StageShape("narrow-1L-h96", 4, 1, 96, 1, 1, 64, 4000)
+# Narrow layers whose prefill gate/up GEMM (M = 2000 rows, 2F = 8000 gate/up rows: ragged in both
+# dimensions, 8 x 32 workgroups) runs on 256 x 256 tiles, the least estimated time at a workgroup for each of
+# 256 compute units.  K in tiles of 32 through three LDS stages: K = 64, two tiles, fewer than stages (all
+# copied at once); 96, three (the pipeline's tail alone); 128 and 160, one and two passes of its loop body.
+NARROW = [synth.StageShape(f"narrow-1L-h{h}", i, 1, h, 1, 1, 64, 4000) for h, i in ((64, 3), (96, 4), (128, 79), (160, 80))]
+# The same tiles over 1000 rows, where the groups of gate/up rows start their k loops at different tiles.
+NARROW_TURN = synth.StageShape("narrow-1L-h320-f8104", 81, 1, 320, 2, 1, 64, 8104)
 
 
-@pytest.mark.parametrize("shape", [NARROW_H64, NARROW_H96], ids=["k64", "k96"])
-def test_prefill_gemm_shortest_pipelined_k_loops(shape):
+@pytest.mark.parametrize("shape,rows", [(s, 2000) for s in NARROW] + [(NARROW_TURN, 1000)],
+                         ids=["k64", "k96", "k128", "k160", "k320-1000-rows"])
+def test_prefill_gemm_shortest_pipelined_k_loops(shape, rows):
     _gpu()
-    plan = [("prefill", 2000), ("decode", 1)]
-    _check(f"{shape.name} prefill 2000", _run(shape, plan, False, 5, 2048))
+    plan = [("prefill", rows), ("decode", 1)]
+    _check(f"{shape.name} prefill {rows}", _run(shape, plan, False, 5, rows + 48))
 
 
 # Prefill GEMM pipeline edges: k loops of 1 to 6 tiles around the three-stage LDS ring (hidden 32 and
@@ -261,9 +264,7 @@ def test_every_attention_group_and_head_width(g, d, kv_fp32):
 # Decode calls of 1 to 40 rows on one small layer whose projections can run on either engine
 # (K a multiple of 128): the vector kernel's 1-, 2-, 4- and 8-row instances, the matrix-core
 # engine from 3 rows (5 for the O projection), its unsplit launches and the down projection's K
-# cut into two ranges, and calls of more
-# than 16 rows cut into several launches (17: 16 + 1; 40: 16 + 16 + 8); every row against the
-# oracle.
+# cut into two ranges; 17 rows as 16 + 1, and 40 as GEMMs; every row against the oracle.
 ROWS_SHAPE = synth.StageShape("rows-1L-h256", 5, 1, 256, 4, 2, 64, 1024)
 
 
@@ -271,6 +272,23 @@ ROWS_SHAPE = synth.StageShape("rows-1L-h256", 5, 1, 256, 4, 2, 64, 1024)
 def test_decode_rows_on_both_engines(rows):
     _gpu()
     _decode_rows(ROWS_SHAPE, rows)
+
+
+# Shapes whose decode calls of more than 16 rows stay on the GEMVs, cut into several launches: an ffn or a
+# query width below the hidden size (17: 16 rows on the matrix cores and 1 on the vector kernel; 20: 16 + 4, the
+# 4 on the vector kernel in the O projection; 40: 16 + 16 + 8), and widths off 128 (the tiny stage's down
+# projection, and every projection of hidden 200: 8 rows at a time on the vector kernel).
+GEMV_ONLY = [synth.StageShape("rows-1L-h256-f128", 82, 1, 256, 4, 2, 64, 128),
+             synth.StageShape("rows-1L-h256-q128", 83, 1, 256, 2, 2, 64, 1024),
+             synth.StageShape("rows-1L-h256-f688", 84, 1, 256, 4, 2, 64, 688),
+             synth.StageShape("rows-1L-h200", 85, 1, 200, 4, 2, 64, 440)]
+
+
+@pytest.mark.parametrize("rows", [17, 20, 40])
+@pytest.mark.parametrize("shape", GEMV_ONLY, ids=["f128", "q128", "f688", "h200"])
+def test_many_rows_on_the_gemvs(shape, rows):
+    _gpu()
+    _decode_rows(shape, rows)
 
 
 # Matrix-core launch forms: an odd number of 128-wide k chunks (the engine takes them in pairs):

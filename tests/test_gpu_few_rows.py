@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import synth
-from tests.harness import Scenario, compare, compute_stream, run_gpu, run_oracle, weights_of
+from tests.harness import Scenario, compare, compute_stream, fp32_close, fp32_errors, run_gpu, run_oracle, weights_of
 
 pytestmark = pytest.mark.gpu
 
@@ -32,6 +32,8 @@ def _check(tag, sc):
     m = compare(got.flat_out(), ref.flat_out(), got.flat_in(), ref.flat_in())
     print(f"\n[{tag}] {m}", flush=True)
     assert m["cos"] >= TOL_COS and m["cos_delta"] >= TOL_COS and m["max_abs"] <= TOL_ABS, m
+    if sc.kv_fp32:
+        assert fp32_close(got.flat_out(), ref.flat_out()), fp32_errors(got.flat_out(), ref.flat_out())
 
 
 # 17, 32 | 33, 64: the edges of the 32- and 64-row tiles; ragged contexts around one 64-key split
@@ -47,12 +49,13 @@ def test_decode_of_more_rows_than_the_gemvs_take(shape, rows, kv_fp32):
            Scenario(wl, prefill=62, decode_steps=4, kv_fp32=kv_fp32, calls="all"))
 
 
+@pytest.mark.parametrize("kv_fp32", [False, True])
 @pytest.mark.parametrize("tokens", [2, 31, 33, 64, 65, 128, 129, 300, 1024, 1025])
 @pytest.mark.parametrize("shape", [CUT_2_2_8, CUT_3_3_4], ids=["2-2-8", "3-3-4"])
-def test_short_prefills(shape, tokens):
+def test_short_prefills(shape, tokens, kv_fp32):
     _gpu()
     wl = synth.Workload(f"{shape.name}-p{tokens}", 171, shape, n_mb=1, batch=1, prefill=tokens, decode_steps=1)
-    _check(f"{shape.name} prefill {tokens}", Scenario(wl, prefill=tokens, decode_steps=1))
+    _check(f"{shape.name} prefill {tokens} fp32={kv_fp32}", Scenario(wl, prefill=tokens, decode_steps=1, kv_fp32=kv_fp32))
 
 
 @pytest.mark.parametrize("shape,n_mb,tokens", [(CUT_WIDE_QKV, 4, 128), (CUT_WIDE_O, 4, 128), (CUT_WIDE_O, 8, 128), (CUT_WIDE_O, 8, 37),
@@ -72,6 +75,19 @@ def test_rows_do_not_depend_on_the_call_they_share(shape, n_mb, tokens):
     m = compare(b, np.asarray(ref.outputs[0]).reshape(-1, shape.hidden),
                 together.inputs[0].reshape(-1, shape.hidden), ref.inputs[0].reshape(-1, shape.hidden))
     assert m["cos"] >= TOL_COS and m["max_abs"] <= TOL_ABS, m
+
+
+# The two lines at which the order of a row's sums changes with the rows beside it: K is cut up to 1024 rows of
+# a call of several tokens, and decode calls run on the GEMVs up to 16 rows and as GEMMs from 19.
+@pytest.mark.parametrize("n_mb,tokens,steps", [(2, 600, 0), (24, 30, 2)], ids=["prefill-600-1200", "decode-1-24"])
+def test_calls_on_either_side_of_a_line(n_mb, tokens, steps):
+    """Micro-batches one per call and all in one call: values that both lie within the fp32 bound of the oracle's."""
+    _gpu()
+    shape = CUT_2_2_8
+    wl = synth.Workload(f"{shape.name}-line{n_mb}", 173, shape, n_mb=n_mb, batch=1, prefill=tokens, decode_steps=max(steps, 1))
+    for calls in ("one", "all"):
+        sc = Scenario(wl, prefill=tokens, decode_steps=max(steps, 1), kv_fp32=True, calls=calls)
+        _check(f"{shape.name} {n_mb} x {tokens}, {calls}", sc)
 
 
 @pytest.mark.parametrize("zero_copy", [False, True])
