@@ -711,9 +711,9 @@ hipError_t launch_gemm(int mode, const GemmArgs &a, int n_mats, hipStream_t st) 
     } else if (a.K % BK != 0) {
         if (mode == GEMM_RESIDUAL) launch_any_k<GEMM_RESIDUAL>(a, n_mats, st);
         else launch_any_k<GEMM_STORE>(a, n_mats, st);
-    } else if (n_mats != 1 || a.out_col[0] != 0) {
+    } else if (n_mats != 1 || a.out_col[0] != 0 || mode != GEMM_RESIDUAL) {   // (the QKV product: launch_qkv)
         return hipErrorInvalidValue;
-    } else if (mode == GEMM_RESIDUAL) {
+    } else {
         const GemmPlan p = gemm_plan(a.M, a.N, a.K, false, a.part != nullptr, a.part_cap64);
         launch_plan<GEMM_RESIDUAL>(a, p, st);
         switch (p.parts()) {
@@ -722,8 +722,6 @@ hipError_t launch_gemm(int mode, const GemmArgs &a, int n_mats, hipStream_t st) 
             case 4: launch_part_residual<4>(a, st); break;
             case 8: launch_part_residual<8>(a, st); break;
         }
-    } else {
-        launch_plan<GEMM_STORE>(a, gemm_plan(a.M, a.N, a.K, false, false, 0), st);
     }
     return hipGetLastError();
 }
