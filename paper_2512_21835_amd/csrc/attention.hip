@@ -352,10 +352,11 @@ __device__ __forceinline__ void split8(const float *x, bf16x8_t &hi, bf16x8_t &l
     }
 }
 
-// 16 bytes that one workgroup reads once per call, non-temporal (16 rows at 7900 tokens of the 70B-shaped
-// stage 118.6 -> 116 us, 64 at about 830 of the 8B-shaped one 44.8 -> 42.8).
-__device__ __forceinline__ u32x4 load_stream16(const uint16_t *p) {
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+// 16 bytes of the cache, which one workgroup reads once per call.  STREAM: non-temporal (see AttnArgs).
+template <bool STREAM>
+__device__ __forceinline__ u32x4 load_cache16(const uint16_t *p) {
+    if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    return *reinterpret_cast<const u32x4 *>(p);
 }
 
 // Decode attention of (up to UNITS consecutive 64-key splits, KV head g, row) on the matrix cores (bf16
@@ -365,7 +366,7 @@ __device__ __forceinline__ u32x4 load_stream16(const uint16_t *p) {
 // outputs as attn_decode_task writes them, or with FINAL the output o / l.  UNITS == kMergeGroup: the
 // state of the whole group of splits, combined as attn_merge combines the splits' own (the same bits),
 // with the K (V) rows of the next split loaded while this one is multiplied.
-template <int G, int D, bool FINAL, int UNITS>
+template <int G, int D, bool FINAL, int UNITS, bool STREAM>
 __global__ __launch_bounds__(256, UNITS == 1 ? 5 : 4) void attn_decode_mfma(AttnArgs a) {
     static_assert(D == 128 && G <= 16, "one 128-wide head, up to 16 query heads per KV head");
     static_assert(UNITS == 1 || (UNITS == kMergeGroup && !FINAL), "one split, or a merge group");
@@ -416,7 +417,7 @@ __global__ __launch_bounds__(256, UNITS == 1 ? 5 : 4) void attn_decode_mfma(Attn
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int key = min(kbeg0 + u * a.split_keys + 16 * wave + 4 * i + lq, ctx - 1);
-            kr[i] = load_stream16(kb + (size_t)(key % kBlockTokens) * D + 8 * (l16 ^ (4 * i + lq)));
+            kr[i] = load_cache16<STREAM>(kb + (size_t)(key % kBlockTokens) * D + 8 * (l16 ^ (4 * i + lq)));
         }
     };
     auto load_v = [&](int u) {
@@ -424,7 +425,7 @@ __global__ __launch_bounds__(256, UNITS == 1 ? 5 : 4) void attn_decode_mfma(Attn
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int key = min(kbeg0 + u * a.split_keys + 16 * wave + 4 * i + lq, ctx - 1);
-            vr[i] = load_stream16(vb + (size_t)(key % kBlockTokens) * D + 8 * l16);
+            vr[i] = load_cache16<STREAM>(vb + (size_t)(key % kBlockTokens) * D + 8 * l16);
         }
     };
     load_k(0);
@@ -1047,11 +1048,18 @@ hipError_t launch_gd(const AttnArgs &a, hipStream_t st) {
         STG_LAUNCH((attn_merge<D, decltype(grouped)::value>), dim3((unsigned)a.n_q_heads, (unsigned)a.rows), dim3(256), 0, st, a);
         return hipGetLastError();
     };
+    [[maybe_unused]] auto mfma = [&](auto units) {
+        constexpr int U = decltype(units)::value;
+        if constexpr (D == 128) {
+            if (a.stream_kv) STG_LAUNCH((attn_decode_mfma<G, D, false, U, true>), grid, dim3(256), 0, st, a);
+            else STG_LAUNCH((attn_decode_mfma<G, D, false, U, false>), grid, dim3(256), 0, st, a);
+        }
+    };
     if (a.grid_splits == 1) {   // every row within one split: its output directly, no merge
         if (a.kv_fp32)
             STG_LAUNCH((attn_decode_kernel<G, D, true, true>), grid, dim3(256), 0, st, a);
         else if constexpr (D == 128)
-            STG_LAUNCH((attn_decode_mfma<G, D, true, 1>), grid, dim3(256), 0, st, a);
+            STG_LAUNCH((attn_decode_mfma<G, D, true, 1, false>), grid, dim3(256), 0, st, a);
         else
             STG_LAUNCH((attn_decode_kernel<G, D, false, true>), grid, dim3(256), 0, st, a);
         return hipGetLastError();
@@ -1067,7 +1075,7 @@ hipError_t launch_gd(const AttnArgs &a, hipStream_t st) {
         const int groups = (a.grid_splits + kMergeGroup - 1) / kMergeGroup;
         if (!a.kv_fp32 && (long)groups * a.n_q_heads * a.rows >= 48L * device_compute_units()) {
             grid.y = groups;
-            STG_LAUNCH((attn_decode_mfma<G, D, false, kMergeGroup>), grid, dim3(256), 0, st, a);
+            mfma(std::integral_constant<int, kMergeGroup>{});
             const hipError_t e = hipGetLastError();
             return e != hipSuccess ? e : merge(std::true_type{});
         }
@@ -1075,7 +1083,7 @@ hipError_t launch_gd(const AttnArgs &a, hipStream_t st) {
     if (a.kv_fp32)
         STG_LAUNCH((attn_decode_kernel<G, D, true, false>), grid, dim3(256), 0, st, a);
     else if constexpr (D == 128)
-        STG_LAUNCH((attn_decode_mfma<G, D, false, 1>), grid, dim3(256), 0, st, a);
+        mfma(std::integral_constant<int, 1>{});
     else
         STG_LAUNCH((attn_decode_kernel<G, D, false, false>), grid, dim3(256), 0, st, a);
     const hipError_t e = hipGetLastError();

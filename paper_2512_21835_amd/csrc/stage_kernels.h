@@ -179,6 +179,7 @@ struct AttnArgs {
     int grid_splits;     // splits launched: ceil(longest context in the call / split_keys)
     int n_seqs;          // sequences in the call and rows per sequence: host copies of the row
     int rows_per_seq;    // metadata (the prefill launch grid; the decode kernels' row -> sequence map)
+    int stream_kv;       // decode over a bf16 cache: read it non-temporally
     RowMap meta;
 };
 hipError_t launch_attention(const AttnArgs &a, hipStream_t st);

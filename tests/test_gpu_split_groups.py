@@ -50,3 +50,43 @@ def test_groups_of_splits_give_the_same_bits(hkv):
             finally:
                 P.stage_destroy(h)
     assert np.isfinite(outs[0]).all() and np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("hkv,rows,held,far", [(32, 2, 300, 2800), (8, 48, 780, 4900)], ids=["splits", "groups"])
+def test_cache_reads_past_the_infinity_cache_give_the_same_bits(hkv, rows, held, far):
+    """The sequences of a call alone on the stage (their cache is read plainly), and beside others with which
+    it holds more than 256 MB (non-temporally); a workgroup per split and per group of splits."""
+    _gpu()
+    import torch
+    import paper_2512_21835_amd as P
+
+    shape = synth.StageShape(f"stream-{hkv}", 640 + hkv, 1, 256, 64, hkv, 128, 512)
+    w = weights_of(shape)(0)
+    others = 6
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+    k, v = (t.view(torch.int16) for t in torch.empty((2, 1, far, hkv, 128), dtype=torch.bfloat16, device="cuda").normal_(generator=gen))
+    x = torch.from_numpy(synth.normal_f32(synth.seed_of(0xFA, 99), (rows, shape.hidden))).cuda()
+    outs = []
+    for beside in (False, True):
+        per_token = 2 * hkv * 128 * 2
+        assert rows * (held + 1) * per_token < 256 << 20 < (rows * (held + 1) + others * far) * per_token
+        with compute_stream() as cs:
+            cfg = P.config_for(shape, max_microbatches=rows + others, max_batch=1, max_context=far + 16, n_resident_max=1,
+                               compute_stream=cs.handle)
+            h = P.stage_init(cfg)
+            try:
+                P.stage_load_layer(h, 0, w, 1)
+                torch.cuda.synchronize()
+                for m in range(rows):
+                    P.stage_kv_append(h, m, 0, held, k[:, :held].contiguous(), v[:, :held].contiguous())
+                for m in range(rows, rows + others if beside else rows):
+                    P.stage_kv_append(h, m, 0, far, k, v)
+                y = torch.empty_like(x)
+                torch.cuda.synchronize()
+                P.stage_decode(h, list(range(rows)), 1, x, y)
+                P.stage_sync(h)
+                outs.append(y.cpu().numpy())
+            finally:
+                P.stage_destroy(h)
+    assert np.isfinite(outs[0]).all() and np.array_equal(outs[0], outs[1])
