@@ -827,13 +827,15 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(AttnArgs a) {
 // products and sums; twice the vector ALUs' rate and none of their operand traffic).  One workgroup: 64
 // query rows = G heads x 64 / G consecutive positions of one sequence, one KV head.  Wavefront w: rows
 // 32 (w % 2) .. + 31 (row r: head r / BQ, position offset r % BQ) over the keys of half w / 2 of each
-// 64-key tile; the two halves' states are merged through LDS at the end (a row's result depends on its
-// position only).  S^T = K Q^T, softmax in-lane, O^T += V^T P^T, where the lane layout of S^T is
+// 64-key tile; the two halves' states are merged through LDS at the end.  Where the call's blocks are few
+// (prefill_key_ranges), the keys are cut into ranges of kRangeKeys, each a workgroup of its own, and attn_merge
+// adds a row's states.  A row's result depends on its position and on which of the two its call is.  S^T = K Q^T, softmax in-lane, O^T += V^T P^T, where the lane layout of S^T is
 // already the one of P^T's operand.  The k index of an MFMA is 8 u + j for lanes 0..31 and 8 u + 4 + j
 // for the rest, so that operands load 16 bytes at a time.
 // Bound by its MFMAs; 68 KB of LDS leave two workgroups per compute unit, one of which multiplies
 // while the other loads.  2 x 600 tokens of the 13B-shaped stage (40 heads): a workgroup per row and
 // KV head on the vector ALUs 700 us -> 186 us, without the pass that made the O projection's operand pair (9 us).
+constexpr int kRangeKeys = 128;   // (whole tiles)
 template <int G, int D>
 __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
     constexpr int KEYS = 64, BQ = 64 / G;
@@ -844,7 +846,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
     static_assert(KEYS * KROW >= 64 * (16 * NB + 2), "a wavefront's state fits where K (V) was");
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wq = wave & 1, kh = wave >> 1;
-    const int qb = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, sidx = blockIdx.y;  // the longest blocks of all first
+    const int ranges = a.grid_splits, range = blockIdx.z % ranges;
+    const int qb = (gridDim.z - 1 - blockIdx.z) / ranges, g = blockIdx.x, sidx = blockIdx.y;  // the longest blocks of all first
     const int T = a.rows_per_seq;
     const int pos0 = a.meta.pos0(sidx), slot = a.meta.seq_slot(sidx);
     const int hkv = a.kv.n_kv_heads, hq_total = a.n_q_heads;
@@ -880,10 +883,13 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
 
     // the last and the first position of the block, the last of this wavefront (keys past it are
     // masked in every one of its rows)
-    const int block_min = pos0 + qb * BQ, n_keys = pos0 + min(T, (qb + 1) * BQ);
+    const int block_min = pos0 + qb * BQ;
+    // the keys that this workgroup takes: first_key .. n_keys - 1
+    const int first_key = range * kRangeKeys, all_keys = pos0 + min(T, (qb + 1) * BQ);
+    const int n_keys = ranges > 1 ? min(all_keys, first_key + kRangeKeys) : all_keys;
     const int wave_max = pos0 + min(T, BQ > 32 ? qb * BQ + 32 * wq + 32 : (qb + 1) * BQ) - 1;
 
-    for (int base = 0; base < n_keys; base += KEYS) {
+    for (int base = first_key; base < n_keys; base += KEYS) {
         __syncthreads();            // the previous tile's LDS reads are done
         // 64 keys x D of K and of V, 16 bytes per access; keys past the block's last: that one (their
         // scores are masked).  A row whose mask hides a key must not meet its V, which may hold an
@@ -985,7 +991,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
                 o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vp[(8 * (i / 4) + i % 4) * VROW32 + 32 * b], s[i], o[b], 0, 0, 0);
     }
 
-    // the second key half's state joins the first's (which holds key 0: never empty)
+    // the second key half's state joins the first's (which holds the first key: empty for no row that sees it)
     __syncthreads();
     float *const st = (wq ? sv : sk) + lane;
     if (kh == 1) {
@@ -997,13 +1003,18 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
         st[64 * (16 * NB + 1)] = l_run;
     }
     __syncthreads();
-    if (kh == 1 || !qvalid) return;
+    if (kh == 1 || !qvalid || first_key > qpos) return;
     const float m1 = st[64 * 16 * NB], l1 = st[64 * (16 * NB + 1)];
     const float m = fmaxf(m_run, m1);
     const bool both = m1 > -INFINITY || l1 != 0.f;   // (l1 is NaN, too, if every score of the half is)
     const float w0 = expf(m_run - m), w1 = both ? expf(m1 - m) : 0.f;
     const float l = both ? fmaf(l1, w1, l_run * w0) : l_run * w0;
     const int k0 = (g * G + hh) * D;
+    const size_t state = (qrow * hq_total + g * G + hh) * a.max_splits + range;   // ranges > 1
+    if (ranges > 1 && half == 0) {
+        a.part_ml[2 * state + 0] = m;
+        a.part_ml[2 * state + 1] = l;
+    }
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -1014,10 +1025,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_f32(AttnArgs a) {
                 const int i = 4 * j + x;
                 v[x] = o[b][i] * w0;
                 if (both) v[x] = fmaf(st[64 * (16 * b + i)], w1, v[x]);
-                v[x] /= l;
+                if (ranges == 1) v[x] /= l;
             }
-            store_pair4(a.out_pair + qrow * a.out_pair_ld + pair_at(k0 + 32 * b + 8 * j + 4 * half),
-                        make_float4(v[0], v[1], v[2], v[3]));
+            const int c = 32 * b + 8 * j + 4 * half;
+            const float4 v4 = make_float4(v[0], v[1], v[2], v[3]);
+            if (ranges > 1) *reinterpret_cast<float4 *>(a.part_o + state * D + c) = v4;
+            else store_pair4(a.out_pair + qrow * a.out_pair_ld + pair_at(k0 + c), v4);
         }
 }
 
@@ -1028,8 +1041,14 @@ hipError_t launch_gd(const AttnArgs &a, hipStream_t st) {
         if (a.n_seqs * a.rows_per_seq != a.rows || a.pair_rows != a.rows) return hipErrorInvalidValue;
         if (a.kv_fp32) {
             constexpr int BQ = 64 / G;
-            dim3 grid(hkv, a.n_seqs, (a.rows_per_seq + BQ - 1) / BQ);
+            if (a.grid_splits < 1) return hipErrorInvalidValue;
+            dim3 grid(hkv, a.n_seqs, (a.rows_per_seq + BQ - 1) / BQ * a.grid_splits);
             STG_LAUNCH((attn_prefill_f32<G, D>), grid, dim3(256), 0, st, a);
+            if (a.grid_splits > 1) {
+                AttnArgs m = a;
+                m.split_keys = kRangeKeys;
+                STG_LAUNCH((attn_merge<D, false>), dim3((unsigned)a.n_q_heads, (unsigned)a.rows), dim3(256), 0, st, m);
+            }
         } else {
             constexpr int BQ = 128 / G;
             dim3 grid(hkv, a.n_seqs, (a.rows_per_seq + BQ - 1) / BQ);
@@ -1102,6 +1121,20 @@ hipError_t launch_attention(const AttnArgs &a, hipStream_t st) {
     STG_ATTN_CASE(1, 128) STG_ATTN_CASE(2, 128) STG_ATTN_CASE(4, 128) STG_ATTN_CASE(8, 128)
 #undef STG_ATTN_CASE
     return hipErrorInvalidValue;
+}
+
+// A block alone takes 3.6 us (d = 64) to 6.5 us (d = 128) per 64 keys, one tile after the other; with few blocks
+// nothing else runs meanwhile, and a workgroup per row, as it was before the tiles, was faster over long contexts.
+// Calls of an fp32 cache, one layer, us, a workgroup per row / blocks with all keys / key ranges: tiny stage, 2
+// tokens after 4000 others 158 / 284 / 65; hkv 2, G 4, d 128, 300 tokens after 4000 490 / 577 / 196; 8B-shaped, 16
+// after 4000 795 / 533 / 141; 13B-shaped, 8 after 8000 1136 / 1094 / 321.  Up to 64 blocks: from 88 on (700 tokens,
+// hkv 2, G 4) all keys in a block beat the workgroup per row at every context (436 against 529 at 4000), and the
+// states of 64 blocks' rows stay below 70 MB per 4000 tokens of context.  Ranges of 256 keys: 5-10 us slower below
+// 500 tokens, 3-5% faster at 3000.
+int prefill_key_ranges(int n_seqs, int T, int longest, int n_q_heads, int n_kv_heads, bool kv_fp32) {
+    const int per = 64 / (n_q_heads / n_kv_heads);   // positions of a query block
+    if (!kv_fp32 || (long)n_kv_heads * n_seqs * ((T + per - 1) / per) > 64) return 1;
+    return (longest + kRangeKeys - 1) / kRangeKeys;
 }
 
 bool attention_supported(int group, int head_dim) {

@@ -174,15 +174,18 @@ struct AttnArgs {
     int n_q_heads;
     int kv_fp32;
     int rows;
-    int split_keys;      // keys per split; 0 = one split per row (final output directly)
+    int split_keys;      // decode: keys per split; prefill: 0
     int max_splits;      // stride of the partial buffers
-    int grid_splits;     // splits launched: ceil(longest context in the call / split_keys)
+    int grid_splits;     // splits launched: ceil(longest context in the call / split_keys); prefill: key ranges
     int n_seqs;          // sequences in the call and rows per sequence: host copies of the row
     int rows_per_seq;    // metadata (the prefill launch grid; the decode kernels' row -> sequence map)
     int stream_kv;       // decode over a bf16 cache: read it non-temporally
     RowMap meta;
 };
 hipError_t launch_attention(const AttnArgs &a, hipStream_t st);
+// Key ranges (AttnArgs::grid_splits, and the states per row that part_o and part_ml hold where it is more
+// than 1) of a prefill of n_seqs x T tokens, the longest sequence at `longest` tokens after it.
+int prefill_key_ranges(int n_seqs, int T, int longest, int n_q_heads, int n_kv_heads, bool kv_fp32);
 bool attention_supported(int group, int head_dim);
 
 // Writes the call's row metadata to device memory (one small launch per call of several sequences; the hot

@@ -511,8 +511,8 @@ size_t part_floats(const stage *s, size_t rows) {
     return n;
 }
 
-int ensure_workspace(stage *s, size_t rows, bool split_attention) {
-    const size_t need_part = split_attention ? rows : 0;
+// need_part: rows of attention partials, max_splits states each.
+int ensure_workspace(stage *s, size_t rows, size_t need_part) {
     if (rows <= s->ws_rows && need_part <= s->part_rows) return STAGE_OK;
     int rc = sync_all(s);
     if (rc) return rc;
@@ -817,7 +817,7 @@ RopeKvArgs rope_args(stage *s, int layer, int rows, const RowMap &meta) {
 
 // Prefill (T >= 2): projections on the matrix cores with bf16 hi/lo operand pairs.
 int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int T, const RowMap &meta,
-                      const float *x_src, float *x_dst) {
+                      int key_ranges, const float *x_src, float *x_dst) {
     const uint16_t *base = w.mha;
     const int H = s->H, F = s->F, qd = s->Hq * s->D;
     const float eps = s->cfg.rms_eps;
@@ -837,7 +837,10 @@ int run_layer_prefill(stage *s, int layer, const LayerWeights &w, int rows, int 
     at.n_q_heads = s->Hq;
     at.kv_fp32 = s->cfg.kv_fp32;
     at.rows = rows;
+    at.part_o = s->ws_part_o;
+    at.part_ml = s->ws_part_ml;
     at.split_keys = 0;
+    at.max_splits = at.grid_splits = key_ranges;
     at.n_seqs = rows / T;
     at.rows_per_seq = T;
     at.meta = meta;
@@ -1071,7 +1074,7 @@ int run_layer_rows(stage *s, int layer, const LayerWeights &w, int rows, const R
 
 int run_layer_kernels(stage *s, int layer, const LayerWeights &w, int rows, int T, const RowMap &meta,
                       int grid_splits, const float *x_src, float *x_dst) {
-    if (T >= 2) return run_layer_prefill(s, layer, w, rows, T, meta, x_src, x_dst);
+    if (T >= 2) return run_layer_prefill(s, layer, w, rows, T, meta, grid_splits, x_src, x_dst);
     if ((size_t)rows > s->part_rows || !s->ws_part_o || !s->ws_part_ml)
         return s->fail(STAGE_ESTATE, "attention partials sized for %zu rows, call has %d", s->part_rows, rows);
     // Timed kernel: the gate/up projection of one layer per call (rotating), so that the events
@@ -1173,7 +1176,7 @@ int run_call_body(stage *s, int n_mb, const int32_t *mb_ids, int B, int T, const
         if (!s->layers[l].loaded) return s->fail(STAGE_EINVAL, "layer %d is not loaded", l);
     int longest = 0;
     for (int len : s->lengths) longest = std::max(longest, len);
-    int need_blocks = 0;
+    int need_blocks = 0, max_ctx = 0;
     for (int sl : slots) {
         const int len = s->lengths[sl] + s->parked[sl];  // a parked tail comes back first
         if (decode && len < 1)
@@ -1182,6 +1185,7 @@ int run_call_body(stage *s, int n_mb, const int32_t *mb_ids, int B, int T, const
             return s->fail(STAGE_ERANGE, "sequence would exceed max_context %d", c.max_context);
         need_blocks += blocks_needed(s, sl, s->parked[sl] + T);
         longest = std::max(longest, len + T);
+        max_ctx = std::max(max_ctx, len + T);
     }
     if (need_blocks > (int)s->free_blocks.size())
         return s->fail(STAGE_ENOMEM, "KV pool exhausted (%d blocks needed, %d free)", need_blocks,
@@ -1189,8 +1193,14 @@ int run_call_body(stage *s, int n_mb, const int32_t *mb_ids, int B, int T, const
     const size_t rows = (size_t)slots.size() * T;
     DeviceGuard dg(c.device);
     // one row per sequence (a decode, or a one-token prefill) runs the decode kernels, whose
-    // attention needs the split partials
-    int rc = ensure_workspace(s, rows, T == 1);
+    // attention needs the split partials; a prefill may need a state per row and key range
+    const int grid_splits = T == 1 ? (max_ctx + kDecodeSplitKeys - 1) / kDecodeSplitKeys
+                                   : prefill_key_ranges((int)slots.size(), T, max_ctx, s->Hq, s->Hkv, c.kv_fp32);
+    if (T == 1 && grid_splits > s->max_splits)
+        return s->fail(STAGE_ESTATE, "attention partials hold %d splits, the call needs %d", s->max_splits, grid_splits);
+    // (for any context, so that they don't grow with every call of a prompt)
+    const size_t states = T == 1 ? s->max_splits : grid_splits > 1 ? prefill_key_ranges(1, 1, c.max_context, s->Hq, s->Hkv, true) : 0;
+    int rc = ensure_workspace(s, rows, (rows * states + s->max_splits - 1) / s->max_splits);
     if (rc) return rc;
     // A zero-copy call with one token per sequence runs offloaded layers on their host blobs and
     // stages nothing; in zero-copy mode the slots are allocated by the first call that stages.
@@ -1236,16 +1246,11 @@ int run_call_body(stage *s, int n_mb, const int32_t *mb_ids, int B, int T, const
     CallMeta meta{};
     meta.n_seqs = (int)slots.size();
     meta.rows_per_seq = T;
-    int max_ctx = 0;
     for (size_t i = 0; i < slots.size(); ++i) {
         meta.seq_slot[i] = slots[i];
         meta.pos0[i] = s->lengths[slots[i]];
         s->lengths[slots[i]] += T;
-        max_ctx = std::max(max_ctx, s->lengths[slots[i]]);
     }
-    const int grid_splits = (max_ctx + kDecodeSplitKeys - 1) / kDecodeSplitKeys;
-    if (T == 1 && grid_splits > s->max_splits)
-        return s->fail(STAGE_ESTATE, "attention partials hold %d splits, the call needs %d", s->max_splits, grid_splits);
     const RowMap row_map{meta.n_seqs > 1 ? s->d_meta : nullptr, T, meta.seq_slot[0], meta.pos0[0]};
     if (row_map.seqs) HIP_TRY(launch_meta_write(meta, s->d_meta, s->cs));
     s->calls++;
