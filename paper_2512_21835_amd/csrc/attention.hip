@@ -298,8 +298,14 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
                 og = make_float4(sum([&](int j) { return o[j].x; }), sum([&](int j) { return o[j].y; }),
                                  sum([&](int j) { return o[j].z; }), sum([&](int j) { return o[j].w; }));
             }
+            if (gi == 0 && s0 == 0) {   // the lane's first: weight 1, nothing before it
+                mx = mg;
+                den = lg;
+                num = og;
+                continue;
+            }
             const float m = fmaxf(mx, mg), ref = m == -INFINITY ? 0.f : m;
-            const float r = expf(mx - ref), w = expf(mg - ref);  // r = 0 on the lane's first group (mx = -inf)
+            const float r = expf(mx - ref), w = expf(mg - ref);
             den = fmaf(w, lg, den * r);
             num.x = fmaf(w, og.x, num.x * r);
             num.y = fmaf(w, og.y, num.y * r);
@@ -313,22 +319,28 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
     s_o[sl][cg] = num;
     __syncthreads();
     if (sl != 0) return;
-    float M = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < SL; ++i) M = fmaxf(M, s_m[i][cg]);
-    const float ref = M == -INFINITY ? 0.f : M;
     float L = 0.f;
     float4 O = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add_lanes = [&](auto count) {
+        constexpr int N = decltype(count)::value;
+        float M = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < SL; ++i) {
-        const float w = expf(s_m[i][cg] - ref);   // (a lane without a group: 0, and its sums are 0)
-        const float4 oi = s_o[i][cg];
-        L = fmaf(w, s_l[i][cg], L);
-        O.x = fmaf(w, oi.x, O.x);
-        O.y = fmaf(w, oi.y, O.y);
-        O.z = fmaf(w, oi.z, O.z);
-        O.w = fmaf(w, oi.w, O.w);
-    }
+        for (int i = 0; i < N; ++i) M = fmaxf(M, s_m[i][cg]);
+        const float ref = M == -INFINITY ? 0.f : M;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float w = expf(s_m[i][cg] - ref);   // (a lane without a group: 0, and its sums are 0)
+            const float4 oi = s_o[i][cg];
+            L = fmaf(w, s_l[i][cg], L);
+            O.x = fmaf(w, oi.x, O.x);
+            O.y = fmaf(w, oi.y, O.y);
+            O.z = fmaf(w, oi.z, O.z);
+            O.w = fmaf(w, oi.w, O.w);
+        }
+    };
+    // rows of up to 4 lanes' groups (1024 keys) leave the empty lanes out, most of the 16 at 64-wide heads
+    if (nst <= 4 * GS) add_lanes(std::integral_constant<int, 4>{});
+    else add_lanes(std::integral_constant<int, SL>{});
     const float4 v = make_float4(O.x / L, O.y / L, O.z / L, O.w / L);
     const int col = hq * D + 4 * cg;
     if (row < a.pair_rows) store_pair4(a.out_pair + row * a.out_pair_ld + pair_at(col), v);
