@@ -1,15 +1,16 @@
-// Prefill projections on the matrix cores: C[M, N] = A[M, K] . W[N, K]^T with bf16 weights W and
+// Projections of prefill, and of decode calls of more than 16 rows, on the matrix cores: C[M, N] =
+// A[M, K] . W[N, K]^T with bf16 weights W and
 // an fp32 activation A taken as the exact-sum pair A = hi + lo of two bf16 matrices (hi = bf16(A),
 // lo = bf16(A - hi); the pair keeps ~16 bits of A's mantissa, a single bf16 only 8).  Each 16-wide
 // k step issues v_mfma_f32_32x32x16_bf16 twice per output block, hi then lo, accumulating in fp32.
 // The pair is stored interleaved by 32-wide k blocks (hi block, then lo block, per row), so the
 // operand bytes of one k tile of a row are 128 contiguous bytes.
 //
-// Tiling: a workgroup (4 wavefronts) computes a 128 x 128 tile of C, each wavefront a 64 x 64
-// sub-tile as 2 x 2 blocks of 32 x 32; or, when the grid of 256 x 256 tiles still has a workgroup
-// for every compute unit, a 256 x 256 tile with 4 x 4 blocks per wavefront.  gemm_tile_kernel (K a
-// multiple of 32) copies tiles global -> LDS directly into a ring of stages; gemm_kernel (any K)
-// stages them through registers into two LDS stages, one tile ahead.  Every fragment read is one
+// Tiling: gemm_tile_kernel (K a multiple of 32), a workgroup of 4 wavefronts per tile of C, copies its
+// operands global -> LDS directly into a ring of three stages.  Up to 32 and 64 rows 32 x 128 and 64 x 128
+// (or 112 columns), beyond that 256 x 256, 128 x 256 or 128 x 128 by the least estimated time; up to
+// kFewRows rows K may be cut into ranges besides (gemm_plan).  gemm_kernel (any K) stages 128 x 128 tiles
+// through registers into two LDS stages, one tile ahead.  Every fragment read is one
 // conflict-free ds_read_b128 per lane.  Workgroups that share a weight tile are adjacent in launch
 // order (x over M tiles), so each weight tile is read from HBM once and re-served from L2.
 //

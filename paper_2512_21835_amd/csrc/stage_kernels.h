@@ -36,8 +36,8 @@ struct CallMeta {
 
 // Where a kernel finds a call's rows: in the device copy of its metadata, or, for a call of one sequence,
 // here.  Such a call, the one whose latency counts, then needs no launch that writes the metadata, and its
-// kernels have one dependent load less ahead of the block table's (70B-shaped layer, four calls of one row
-// 1078 -> 1069 us; tiny stage's 16-token prompt and 16 steps 739 -> 711).
+// kernels have one dependent load less ahead of the block table's (a step of the tiny stage 43.3 -> 41.3 us; of
+// 8B- and 70B-shaped stages, 665 and 270 us, within the runs' noise).
 struct RowMap {
     const CallMeta *seqs;   // null: one sequence
     int rows_per_seq, slot, first;
@@ -133,6 +133,11 @@ hipError_t launch_gemm(int mode, const GemmArgs &a, int n_mats, hipStream_t st);
 // Rows up to which K is cut into ranges.  The cut depends on the matrix only, not on the rows, and
 // the partial products are always added in the same order, so a row's result is the same for any
 // number of rows up to kFewRows (and the same for any number beyond, where K is whole).
+// Why 1024: beyond it the whole K has tiles enough, and the adding of the parts costs more than the fuller
+// grid gives.  One layer, us, whole K / cut: 8B-shaped 1025 rows 1015 / 1113, 1500 1301 / 1297, 2048 1548 / 1601;
+// 13B-shaped 1025 1420 / 1435, 1500 1683 / 1716; 70B-shaped 1025 3652 / 3763, 1300 4220 / 4121, 2048 5234 / 5292; only
+// the 32B-shaped layer gains from 1800 (3460 / 3337).  Up to it the cut wins: 1024 rows 8B-shaped 1004 (former tiles)
+// / 870, 70B-shaped 3380 / 2974.
 constexpr int kFewRows = 1024;
 // Floats of GemmArgs::part that no call of up to `rows` rows exceeds for a matrix [N, K], or `most` if that
 // is more.  cap64: what the cut assumes for up to 64 rows (it takes fewer ranges where they would not fit).
